@@ -14,6 +14,8 @@
 // memory (16-byte per-lane loads); the adapter factor feeds the MFMA A slot,
 // the activation rows the B slot, so each lane ends with 4 consecutive
 // output columns of one row.  fp32: plain per-thread dot products.
+#include <algorithm>
+
 #include "vfm_internal.h"
 
 namespace {
@@ -347,80 +349,115 @@ __global__ __launch_bounds__(256) void expand_f32_kernel(Plan pl, ExpandArgs a) 
 
 // ---------------------------------------------------------------------------
 // heads: out[out_off[order[p]] + n] = pooled[p] . W_t[n] + b_t[n]
-// One block per (task, 64-column chunk); the block walks the task's
-// requests 16 at a time; each wave owns 16 of the 64 columns.
+//
+// HID: the MLP heads' first layer, hid[p, n] = act(pooled[p] . W1_t[n] +
+// b1_t[n]) for tasks with an MLP head; otherwise the output layer, out =
+// in[p] . W_t[n] + b_t[n] with `in` the pooled row (linear head) or the
+// hidden row (MLP head).
+//
+// Bound by the tasks' weights, each read once, and by the latency of the
+// chain over K.  One block per (task, 16 outputs): its 8 waves split K and
+// add their sums in wave order through LDS, so a wave's chain is K / 8 and
+// the chip holds outputs / 16 times 8 waves per task (256 requests of 71
+// tasks, 256 outputs of K = 4096: 1136 blocks; 214.8 us with a wave walking
+// the whole K for 16 outputs, 36.9 us = 4.1 TB/s of weights so).  Up to
+// HEAD_NG groups of 16 requests share a pass over the weights (2 instead of
+// 4: 10 us more, the task of 55 requests then reads its weights twice).  A
+// request's sums depend on K alone, never on the other requests.
 // ---------------------------------------------------------------------------
-// Head GEMMs of one task's requests.  HID: the MLP heads' first layer,
-// hid[p, n] = act(pooled[p] . W1_t[n] + b1_t[n]) for tasks with an MLP head;
-// otherwise the output layer, out = in[p] . W_t[n] + b_t[n] with `in` the
-// pooled row (linear head) or the hidden row (MLP head).
+constexpr int HEAD_WAVES = 8;
+constexpr int HEAD_NG = 4;
+
+// acc[j] = the wave's share of K (32-column steps k0 .. k1) of 16 outputs
+// times the 16 requests of group j
+template <int NG>
+__device__ __forceinline__ void head_dots(const bf16* wrow, const bf16* const (&xrow)[HEAD_NG], int k0, int k1,
+                                          f32x4 (&acc)[HEAD_NG]) {
+  constexpr int U = NG <= 2 ? 8 : 4;                    // steps whose loads are in flight together
+  int k = k0;
+  for (; k + 32 * U <= k1; k += 32 * U) {
+    bf16x8 wf[U], xf[U][NG];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      wf[u] = *reinterpret_cast<const bf16x8*>(wrow + k + 32 * u);
+#pragma unroll
+      for (int j = 0; j < NG; ++j) xf[u][j] = *reinterpret_cast<const bf16x8*>(xrow[j] + k + 32 * u);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < NG; ++j) acc[j] = mfma16(wf[u], xf[u][j], acc[j]);
+  }
+  for (; k < k1; k += 32) {
+    const bf16x8 wf = *reinterpret_cast<const bf16x8*>(wrow + k);
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+      acc[j] = mfma16(wf, *reinterpret_cast<const bf16x8*>(xrow[j] + k), acc[j]);
+  }
+}
+
 template <bool HID>
-__global__ __launch_bounds__(256) void heads_bf16_kernel(Plan pl, const bf16* __restrict__ pooled,
-                                                         int d, vfm_head_table h, bf16* __restrict__ hid,
-                                                         float* __restrict__ out) {
-  __shared__ f32x4 red[4][64];
-  const int t = blockIdx.x;
-  const bool mlp = h.W1 != nullptr && h.W1[t] != nullptr;
-  if (HID && !mlp) return;                            // block-uniform
-  const int n_out = HID ? h.hidden : h.n_out[t];
-  const int n0 = blockIdx.y * 64;
+__global__ __launch_bounds__(64 * HEAD_WAVES) void heads_bf16_kernel(Plan pl, const bf16* __restrict__ pooled,
+                                                                    int d, vfm_head_table h, int nchunk,
+                                                                    bf16* __restrict__ hid,
+                                                                    float* __restrict__ out) {
+  __shared__ f32x4 red[HEAD_WAVES][HEAD_NG][64];
+  // a task's blocks follow each other, in task order: the tasks of skewed
+  // mixes that own most requests (the first ids under a Zipf law) start first
+  const int t = blockIdx.x / nchunk, chunk = blockIdx.x % nchunk;
+  // every table entry is requested before the first is used
   const int p0 = pl.seg_req[t], p1 = pl.seg_req[t + 1];
-  if (p0 == p1 || n0 >= n_out) return;                // block-uniform
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bf16* Wt = (const bf16*)(HID ? h.W1[t] : h.W[t]);
+  const void* const w1 = h.W1 != nullptr ? h.W1[t] : nullptr;
+  const void* const w0 = HID ? nullptr : h.W[t];
+  const int no = HID ? h.hidden : h.n_out[t];
   const bf16* bt = HID ? (h.b1 ? (const bf16*)h.b1[t] : nullptr) : (h.b ? (const bf16*)h.b[t] : nullptr);
+  const bool mlp = w1 != nullptr;
+  if (p0 == p1 || chunk * 16 >= no || (HID && !mlp)) return;   // block-uniform
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bf16* Wt = (const bf16*)(HID ? w1 : w0);
   const bool from_hid = !HID && mlp;
-  const int K = from_hid ? h.hidden : d;
+  const int K = from_hid ? h.hidden : d;              // a multiple of 64
   const bf16* in = from_hid ? hid : pooled;
-  // at most 16 outputs left in this block: the 4 waves split K over the same
-  // 16 rows and add their sums in wave order; otherwise each wave owns 16 rows
-  const bool ksplit = n_out - n0 <= 16 && K % 128 == 0;
-  const int rb = ksplit ? n0 : n0 + wave * 16;        // the wave's first output row
-  const int kq = ksplit ? K / 4 : K;                  // K per wave
-  const int kb = ksplit ? wave * kq : 0;
-  const int nrow = rb + (lane & 15);
-  const bf16* wrow = Wt + (int64_t)min(nrow, n_out - 1) * K + kb + 8 * (lane >> 4);
-  for (int pb = p0; pb < p1; pb += 16) {
-    const int p = pb + (lane & 15);
-    const bf16* xrow = in + (int64_t)min(p, p1 - 1) * K + kb + 8 * (lane >> 4);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int k = 0; k < kq; k += 32) {
-      const bf16x8 wf = *reinterpret_cast<const bf16x8*>(wrow + k);
-      const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xrow + k);
-      acc = mfma16(wf, xf, acc);
-    }
-    if (ksplit) {
-      red[wave][lane] = acc;
-      __syncthreads();
-      if (wave == 0) {
+  const int k0 = wave * (K / 32) / HEAD_WAVES * 32, k1 = (wave + 1) * (K / 32) / HEAD_WAVES * 32;
+  for (int n0 = chunk * 16; n0 < no; n0 += nchunk * 16)
+  for (int pb = p0; pb < p1; pb += 16 * HEAD_NG) {
+    const bf16* wrow = Wt + (int64_t)min(n0 + (lane & 15), no - 1) * K + 8 * (lane >> 4);
+    const bf16* xrow[HEAD_NG];
+    f32x4 acc[HEAD_NG];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
-          const f32x4 u = red[w][lane];
-          acc[0] += u[0]; acc[1] += u[1]; acc[2] += u[2]; acc[3] += u[3];
-        }
+    for (int j = 0; j < HEAD_NG; ++j) {
+      xrow[j] = in + (int64_t)min(pb + 16 * j + (lane & 15), p1 - 1) * K + 8 * (lane >> 4);
+      acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int ng = min((p1 - pb + 15) / 16, HEAD_NG);   // block-uniform
+    // where this wave's group goes, read ahead of the products
+    const int p = pb + 16 * (wave % HEAD_NG) + (lane & 15), nb = n0 + 4 * (lane >> 4);
+    const int req = HID ? 0 : pl.order[min(p, p1 - 1)];
+    const int o0 = HID ? 0 : pl.out_off[req], o1 = HID ? 0 : pl.out_off[req + 1];
+    if (ng == 1) head_dots<1>(wrow, xrow, k0, k1, acc);
+    else if (ng == 2) head_dots<2>(wrow, xrow, k0, k1, acc);
+    else head_dots<HEAD_NG>(wrow, xrow, k0, k1, acc);
+#pragma unroll
+    for (int j = 0; j < HEAD_NG; ++j)
+      if (j < ng) red[wave][j][lane] = acc[j];
+    __syncthreads();
+    if (wave < ng && p < p1) {                         // wave j finishes group j
+      f32x4 v = red[0][wave][lane];
+#pragma unroll
+      for (int w = 1; w < HEAD_WAVES; ++w) {
+        const f32x4 u = red[w][wave][lane];
+        v[0] += u[0]; v[1] += u[1]; v[2] += u[2]; v[3] += u[3];
       }
-      __syncthreads();                                // red is reused by the next group
-    }
-    if (p < p1 && (!ksplit || wave == 0)) {
-      if (HID) {
+      const int lim = HID ? no : min(no, o1 - o0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int n = rb + 4 * (lane >> 4) + i;
-          const float v = acc[i] + (bt ? (float)bt[n] : 0.f);
-          hid[(int64_t)p * h.hidden + n] = (bf16)(h.act == VFM_ACT_RELU ? fmaxf(v, 0.f) : gelu_fast(v));
-        }
-      } else {
-        const int req = pl.order[p];
-        const int lim = min(n_out, pl.out_off[req + 1] - pl.out_off[req]);
-        float* o = out + pl.out_off[req];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int n = rb + 4 * (lane >> 4) + i;
-          if (n < lim) o[n] = acc[i] + (bt ? (float)bt[n] : 0.f);
-        }
+      for (int i = 0; i < 4; ++i) {
+        if (nb + i >= lim) break;
+        const float y = v[i] + (bt ? (float)bt[nb + i] : 0.f);
+        if (HID) hid[(int64_t)p * h.hidden + nb + i] = (bf16)(h.act == VFM_ACT_RELU ? fmaxf(y, 0.f) : gelu_fast(y));
+        else out[o0 + nb + i] = y;
       }
     }
+    __syncthreads();                                   // red is reused by the next groups
   }
 }
 
@@ -542,23 +579,25 @@ hipError_t launch_heads(int dtype, const Plan& pl, const void* pooled, int d,
                         const vfm_head_table& h, float* out, hipStream_t s) {
   const size_t es = dtype == VFM_BF16 ? 2 : 4;
   char* hid = (char*)pooled + (((size_t)pl.n_req * d * es + 255) & ~(size_t)255);
+  // blocks per task: one per 16 outputs, fewer (each then takes several
+  // chunks) only where tasks x chunks would outgrow a grid
+  auto chunks = [&](int n) { return std::max(1, std::min((n + 15) / 16, (1 << 22) / h.n_tasks)); };
+  const int nh = chunks(h.hidden), no = chunks(h.max_out);
   if (h.W1 && h.hidden > 0) {
-    dim3 g1(h.n_tasks, (h.hidden + 63) / 64);
     if (dtype == VFM_BF16)
-      hipLaunchKernelGGL((heads_bf16_kernel<true>), g1, dim3(256), 0, s, pl, (const bf16*)pooled, d, h,
-                         (bf16*)hid, out);
+      hipLaunchKernelGGL((heads_bf16_kernel<true>), dim3(h.n_tasks * nh), dim3(64 * HEAD_WAVES), 0, s, pl,
+                         (const bf16*)pooled, d, h, nh, (bf16*)hid, out);
     else
-      hipLaunchKernelGGL((heads_f32_kernel<true>), g1, dim3(256), 0, s, pl, (const float*)pooled, d, h,
-                         (float*)hid, out);
+      hipLaunchKernelGGL((heads_f32_kernel<true>), dim3(h.n_tasks, (h.hidden + 63) / 64), dim3(256), 0, s, pl,
+                         (const float*)pooled, d, h, (float*)hid, out);
   }
-  dim3 grid(h.n_tasks, (h.max_out + 63) / 64);
-  if (grid.y == 0) return hipGetLastError();
+  if (h.max_out == 0) return hipGetLastError();
   if (dtype == VFM_BF16)
-    hipLaunchKernelGGL((heads_bf16_kernel<false>), grid, dim3(256), 0, s, pl, (const bf16*)pooled, d, h,
-                       (bf16*)hid, out);
+    hipLaunchKernelGGL((heads_bf16_kernel<false>), dim3(h.n_tasks * no), dim3(64 * HEAD_WAVES), 0, s, pl,
+                       (const bf16*)pooled, d, h, no, (bf16*)hid, out);
   else
-    hipLaunchKernelGGL((heads_f32_kernel<false>), grid, dim3(256), 0, s, pl, (const float*)pooled, d, h,
-                       (float*)hid, out);
+    hipLaunchKernelGGL((heads_f32_kernel<false>), dim3(h.n_tasks, (h.max_out + 63) / 64), dim3(256), 0, s, pl,
+                       (const float*)pooled, d, h, (float*)hid, out);
   return hipGetLastError();
 }
 

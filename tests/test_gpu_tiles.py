@@ -1,0 +1,61 @@
+"""GPU tests of kernel choices at the sizes where they can go wrong: edges of
+tiles, remainders, the smallest and largest of a rule's range, against the
+fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import vfm_oracle as O
+from paper_2606_09643_amd import binding as B
+from paper_2606_09643_amd import runner as R
+from paper_2606_09643_amd import workloads as wl
+from tests.gpu_common import log, oracle_plan, seeded_rows, set_rows, tol
+from tests.helpers import np64, spec_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("idx,d,pool,hidden", [(2, 64, "first", 64), (2, 768, "last", 0), (5, 4096, "last", 128),
+                                               (3, 1024, "mean", 0), (1, 256, "first", 64)])
+def test_heads_output_and_request_remainders(idx, d, pool, hidden):
+    """Head widths around the 16-output blocks (1, 15, 16, 17, 250), tasks of
+    0, 1, 16, 17, 65 and 130 requests (groups of 16, up to 64 in one pass),
+    linear and MLP heads side by side, one-row and mean pooling."""
+    w = wl.WORKLOADS[idx].replace(d=d, n_heads=d // 64, head_dim=64, n_tasks=6, pool=pool, mode="prefill")
+    n_out = np.array([17, 250, 1, 16, 15, 33], np.int32)
+    counts = [65, 1, 17, 16, 130, 0]
+    r = np.random.default_rng(5)
+    task = r.permutation(np.repeat(np.arange(6), counts)).astype(np.int32)
+    batch = wl.Batch(task, r.integers(1, 4, size=len(task)).astype(np.int32), None)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    t_ = lambda *shape, std: (torch.randn(*shape, generator=g, device="cuda") * std).to(w.torch_dtype)  # noqa: E731
+    mlp = [hidden > 0 and t % 2 == 0 for t in range(6)]
+    Ws = [t_(int(n), hidden if m else d, std=(hidden if m else d) ** -0.5) for n, m in zip(n_out, mlp)]
+    bs = [t_(int(n), std=0.1) if t != 3 else None for t, n in enumerate(n_out)]
+    W1 = [t_(hidden, d, std=d ** -0.5) if m else None for m in mlp] if hidden else None
+    b1 = [t_(hidden, std=0.1) if m else None for m in mlp] if hidden else None
+    tab = B.HeadTable(n_out, Ws, bs, R._POOL[pool], W1s=W1, b1s=b1, hidden=hidden)
+    final = wl.final_norm(w, "cuda")
+    pb = B.Batch(batch.task_id, batch.seq_len, 6, n_out=n_out)
+    x = torch.empty(pb.T, d, device="cuda")
+    rows = seeded_rows(pb.T, d, 11)
+    set_rows(x, rows)
+    cfg = R.cfg_for(w)
+    ws = torch.empty(B.vfm_workspace_size(cfg, pb.c), dtype=torch.uint8, device="cuda")
+    out = torch.full((pb.total_outputs,), float("nan"), device="cuda")
+    log(f"heads d={d} pool={pool} hidden={hidden}")
+    B.vfm_head_forward(cfg, final["w"], final["b"], tab.c, pb.c, x, out, ws)
+    got = out.cpu().numpy()
+    pl = oracle_plan(w, batch, n_out)
+    cu, off, spec = pl["cu_seqlens"], pl["logit_off"], spec_of(w)
+    fb = np64(final["b"]) if final["b"] is not None else None
+    ref = np.empty(len(got))
+    for p, i in enumerate(pl["order"]):
+        t = int(pl["task"][p])
+        v = O.pool(O.final(spec, np64(final["w"]), fb, rows[int(cu[p]):int(cu[p + 1])]), pool)
+        b = np64(bs[t]) if bs[t] is not None else np.zeros(int(n_out[t]))
+        ref[off[i]:off[i + 1]] = (O.head_mlp(v, np64(W1[t]), np64(b1[t]), np64(Ws[t]), b) if mlp[t]
+                                  else O.head(v, np64(Ws[t]), b))
+    err = np.abs(got - ref).max() / np.abs(ref).max()
+    log(f"  max rel err {err:.3e}")
+    assert err < tol(w)
