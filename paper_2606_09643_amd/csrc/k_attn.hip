@@ -584,13 +584,117 @@ __global__ __launch_bounds__(64 * NW) void attn_short_bf16_kernel(Plan pl, const
 }
 
 // ---------------------------------------------------------------------------
-// Prefill attention, generic SIMT (fp32 workloads): 64 queries per block,
-// 4 threads per query, each owning DH/4 dims; keys staged in LDS.
+// Bidirectional prefill attention, fp32 (v_mfma_f32_16x16x4_f32): one wave
+// per 16 queries of one request and one head, operands from global memory
+// straight into registers, online softmax over 16 KT keys a step.
+//
+// The fp32 encoder's 64-token requests are far too small to fill the chip, so
+// the chain of one wave is the time: the SIMT kernel below walks the keys one
+// by one (two shuffles and two exponentials each, 32.6 us for 16 requests x 4
+// heads of 64 tokens), this one KT x 16 keys at a time (7.6 us).
+//
+// S^T = K Q^T with K rows in the A slot, so a lane (g = lane / 16) holds keys
+// 4 g .. 4 g + 3 of one query; a 16-byte load of K or Q holds 4 consecutive
+// head dims, MFMA e taking component e of both.  P^T is then the B operand of
+// O^T = V^T P^T as it lies: MFMA j takes keys {4 g + j}.  A lane loads dims
+// 4 x .. 4 x + 3 (x = lane % 16) of its key's V row and MFMA tile c takes
+// component c, i.e. row x of tile c is head dim 4 x + c, which leaves a lane
+// with 16 consecutive head dims of its query.
 // ---------------------------------------------------------------------------
-template <typename T, int DH>
-__global__ __launch_bounds__(256) void attn_prefill_simt_kernel(Plan pl, const T* __restrict__ qkv,
-                                                                int d, T* __restrict__ out,
-                                                                float scale_log2, int causal) {
+template <int DH>
+__global__ __launch_bounds__(64) void attn_bidir_f32_kernel(Plan pl, const float* __restrict__ qkv, int d,
+                                                            float* __restrict__ out, float scale_log2) {
+  constexpr int KT = DH == 64 ? 4 : 2, NC = DH / 16, NH = DH / 64;
+  auto mfma = [](float a, float b, const f32x4& c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); };
+  const int b = blockIdx.x >> 2, h = blockIdx.y;
+  const int p = upper_index(pl.qblk_off, pl.n_req + 1, b);
+  const int R = pl.cu_seqlens[p], L = pl.cu_seqlens[p + 1] - R;
+  const int q0 = (b - pl.qblk_off[p]) * 64 + (blockIdx.x & 3) * 16;
+  if (q0 >= L) return;
+  const int lane = threadIdx.x, x = lane & 15, g = lane >> 4;
+  const int64_t ld = 3 * (int64_t)d;
+  const float* base = qkv + (int64_t)R * ld + h * DH;
+  const int qi = q0 + x;
+  f32x4 q[NC], o[NH][4];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    q[c] = *reinterpret_cast<const f32x4*>(base + (int64_t)min(qi, L - 1) * ld + 16 * c + 4 * g);
+#pragma unroll
+  for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) o[hh][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = NEG_BIG, l_run = 0.f;
+  for (int kb = 0; kb < L; kb += 16 * KT) {
+    // keys past L re-read the last one (masked: weight 0)
+    f32x4 st[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      const float* kr = base + (int64_t)min(kb + 16 * kt + x, L - 1) * ld + d + 4 * g;
+      f32x4 kf[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) kf[c] = *reinterpret_cast<const f32x4*>(kr + 16 * c);
+      f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a = mfma(kf[c][e], q[c][e], a);
+      st[kt] = a;
+    }
+    float mb = NEG_BIG;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        st[kt][i] = kb + 16 * kt + 4 * g + i < L ? st[kt][i] * scale_log2 : -INFINITY;
+        mb = fmaxf(mb, st[kt][i]);
+      }
+    mb = fmaxf(mb, __shfl_xor(mb, 16, 64));
+    mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
+    const float m_new = fmaxf(m_run, mb);
+    const float alpha = exp2f(m_run - m_new);
+    m_run = m_new;
+    l_run *= alpha;
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[hh][c] *= alpha;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float e = exp2f(st[kt][j] - m_new);
+        l_run += e;
+        const float* vr = base + (int64_t)min(kb + 16 * kt + 4 * g + j, L - 1) * ld + 2 * d + 4 * x;
+#pragma unroll
+        for (int hh = 0; hh < NH; ++hh) {
+          const f32x4 vf = *reinterpret_cast<const f32x4*>(vr + 64 * hh);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) o[hh][c] = mfma(vf[c], e, o[hh][c]);
+        }
+      }
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (qi >= L) return;
+  float* orow = out + (int64_t)(R + qi) * d + h * DH + 16 * g;
+#pragma unroll
+  for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      *reinterpret_cast<f32x4*>(orow + 64 * hh + 4 * r) =
+          f32x4{o[hh][0][r], o[hh][1][r], o[hh][2][r], o[hh][3][r]} / l_run;
+}
+
+// ---------------------------------------------------------------------------
+// Causal prefill attention, fp32, SIMT: 64 queries per block, 4 threads per
+// query, each owning DH/4 dims; keys staged in LDS.  A query never touches a
+// later key (an MFMA over a tile with masked keys multiplies their V rows by
+// zero, which an infinity there would turn into NaN).
+// ---------------------------------------------------------------------------
+template <int DH>
+__global__ __launch_bounds__(256) void attn_causal_f32_kernel(Plan pl, const float* __restrict__ qkv,
+                                                                int d, float* __restrict__ out,
+                                                                float scale_log2) {
   constexpr int DQ = DH / 4;
   __shared__ float Ks[64][DH + 1];
   __shared__ float Vs[64][DH + 1];
@@ -602,19 +706,19 @@ __global__ __launch_bounds__(256) void attn_prefill_simt_kernel(Plan pl, const T
   const int tid = threadIdx.x, qi = q0 + (tid >> 2), part = tid & 3;
   const int64_t ld = 3 * (int64_t)d;
   float q[DQ], o[DQ];
-  const T* qrow = qkv + (int64_t)(R + min(qi, L - 1)) * ld + h * DH + part * DQ;
+  const float* qrow = qkv + (int64_t)(R + min(qi, L - 1)) * ld + h * DH + part * DQ;
 #pragma unroll
-  for (int i = 0; i < DQ; ++i) { q[i] = to_f32(qrow[i]); o[i] = 0.f; }
+  for (int i = 0; i < DQ; ++i) { q[i] = qrow[i]; o[i] = 0.f; }
   float m_run = NEG_BIG, l_run = 0.f;
-  const int kend = causal ? min(L, q0 + 64) : L;
+  const int kend = min(L, q0 + 64);
   for (int kb = 0; kb < kend; kb += 64) {
     for (int e = tid; e < 64 * DH; e += 256) {
       const int key = e / DH, c = e % DH;
       float kv = 0.f, vv = 0.f;
       if (kb + key < L) {
-        const T* src = qkv + (int64_t)(R + kb + key) * ld + h * DH + c;
-        kv = to_f32(src[d]);
-        vv = to_f32(src[2 * d]);
+        const float* src = qkv + (int64_t)(R + kb + key) * ld + h * DH + c;
+        kv = src[d];
+        vv = src[2 * d];
       }
       Ks[key][c] = kv;
       Vs[key][c] = vv;
@@ -629,7 +733,7 @@ __global__ __launch_bounds__(256) void attn_prefill_simt_kernel(Plan pl, const T
       s += __shfl_xor(s, 1, 64);
       s += __shfl_xor(s, 2, 64);
       s *= scale_log2;
-      if (causal && key > qi) continue;
+      if (key > qi) continue;
       const float m_new = fmaxf(m_run, s);
       const float alpha = exp2f(m_run - m_new), e = exp2f(s - m_new);
       l_run = l_run * alpha + e;
@@ -640,9 +744,9 @@ __global__ __launch_bounds__(256) void attn_prefill_simt_kernel(Plan pl, const T
     __syncthreads();
   }
   if (qi < L) {
-    T* orow = out + (int64_t)(R + qi) * d + h * DH + part * DQ;
+    float* orow = out + (int64_t)(R + qi) * d + h * DH + part * DQ;
 #pragma unroll
-    for (int i = 0; i < DQ; ++i) orow[i] = from_f32<T>(o[i] / l_run);
+    for (int i = 0; i < DQ; ++i) orow[i] = o[i] / l_run;
   }
 }
 
@@ -1040,12 +1144,14 @@ hipError_t launch_attention(int dtype, const Plan& pl, const vfm_cfg& c, const v
 #undef PRE
     }
     if (dtype != VFM_BF16) {
-      if (DH == 64)
-        hipLaunchKernelGGL((attn_prefill_simt_kernel<float, 64>), grid, dim3(256), 0, s, pl,
-                           (const float*)qkv, d, (float*)out, scale_log2, (int)causal);
-      else
-        hipLaunchKernelGGL((attn_prefill_simt_kernel<float, 128>), grid, dim3(256), 0, s, pl,
-                           (const float*)qkv, d, (float*)out, scale_log2, (int)causal);
+#define F32(K_, G_, B_, D_) \
+  hipLaunchKernelGGL((K_<D_>), G_, dim3(B_), 0, s, pl, (const float*)qkv, d, (float*)out, scale_log2)
+      if (causal) { if (DH == 64) F32(attn_causal_f32_kernel, grid, 256, 64); else F32(attn_causal_f32_kernel, grid, 256, 128); }
+      else {
+        dim3 g4(4 * pl.n_qblocks, H);
+        if (DH == 64) F32(attn_bidir_f32_kernel, g4, 64, 64); else F32(attn_bidir_f32_kernel, g4, 64, 128);
+      }
+#undef F32
     }
     // prompt chunks after cached tokens: their rows again, over every key
     // of the request read from the cache (the rows above attended to the

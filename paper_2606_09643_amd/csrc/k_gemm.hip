@@ -21,8 +21,8 @@
 // up with 4 consecutive output columns of one row: epilogue stores are 8-byte
 // (bf16) or 16-byte (fp32) vectors.
 //
-// fp32 path: a plain LDS-tiled FMA GEMM with the same epilogues (the tiny
-// fp32 encoder workload only needs exactness, not speed).
+// fp32 path: fp32 MFMA with small tiles and K split over a block's waves
+// (gemm_f32_kernel), the same epilogues.
 #include <type_traits>
 
 #include "vfm_internal.h"
@@ -775,117 +775,143 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32: LDS-tiled FMA GEMM, 64x64 tile, 4x4 outputs per thread.
+// fp32: v_mfma_f32_16x16x4_f32 (fp32 products and sums), (16 FM) x (16 FN)
+// outputs per block, the block's 4 waves each taking a quarter of K and
+// adding their sums in wave order through LDS.
+//
+// The fp32 batches are small (1024 rows of a 256-wide encoder: 0.13 - 0.54
+// GFLOP a product), so the kernel is bound by the latency of its chain over
+// K, not by the matrix units: small tiles and the K split give every CU
+// blocks and shorten the chain fourfold, and operands go from global memory
+// (L2) straight into registers with no barrier.  A lane's 16-byte load holds
+// 4 consecutive k of one row; MFMA j of a 16-column step takes component j of
+// both operands, i.e. the columns {4 g + j}, which only reorders the sum.
+// 64x64 FMA tiles with two barriers per 16 columns took 39.5 / 18.9 / 23.2 /
+// 63.2 us for that encoder's QKV / O / up / down, this kernel 14.0 / 5.5 /
+// 14.0 / 11.5 us (60 TFLOP/s at 4096 rows).  A row's sums depend on K alone: the tile shape, chosen by the
+// number of blocks, does not change them.
 // ---------------------------------------------------------------------------
-template <int EPI, bool SWIGLU>
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// s_t (x A_t^T) B_t^T of row m, columns nrow .. nrow + 3 of one LoRA slot
+__device__ __forceinline__ f32x4 lora_f32(const GemmLora& L, int slot, int m, int nrow) {
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  const int t = L.row_task[m];
+  const int r = min(L.rank[t], L.max_rank) & ~7;
+  if (r <= 0 || L.B[slot] == nullptr) return s;
+  const float* Bt = (const float*)L.B[slot][t] + (int64_t)nrow * r;
+  const float* u = (const float*)L.U + (int64_t)m * L.ldu + L.ucol[slot];
+  for (int q = 0; q < r; q += 4) {
+    const f32x4 uv = *reinterpret_cast<const f32x4*>(u + q);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const f32x4 bv = *reinterpret_cast<const f32x4*>(Bt + (int64_t)c * r + q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[c] = fmaf(uv[e], bv[e], s[c]);
+    }
+  }
+  return s;
+}
+
+template <int EPI, bool SWIGLU, int FM, int FN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  constexpr int TM = 64, TN = 64, TK = 16;
-  __shared__ float Xs[TK][TM + 4];
-  __shared__ float Ws[TK][TN + 4];
-  __shared__ float W2s[SWIGLU ? TK : 1][TN + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int n_tiles_n = (a.N + TN - 1) / TN;
-  const int tn = blockIdx.x % n_tiles_n, tm = blockIdx.x / n_tiles_n;
-  const int m0 = tm * TM, n0 = tn * TN;
-  const float* X = (const float*)a.X;
-  const float* W = (const float*)a.W;
-  const float* W2 = (const float*)a.W2;
-  const int lrow = tid >> 2, kq = (tid & 3) * 4;
-  const int xm = min(m0 + lrow, a.M - 1), wn_ = min(n0 + lrow, a.N - 1);
-  float acc[4][4] = {}, acc2[4][4] = {};
-  for (int k0 = 0; k0 < a.K; k0 += TK) {
-    const float4 xv = *reinterpret_cast<const float4*>(X + (int64_t)xm * a.ldx + k0 + kq);
-    const float4 wv = *reinterpret_cast<const float4*>(W + (int64_t)wn_ * a.K + k0 + kq);
-    Xs[kq + 0][lrow] = xv.x; Xs[kq + 1][lrow] = xv.y; Xs[kq + 2][lrow] = xv.z; Xs[kq + 3][lrow] = xv.w;
-    Ws[kq + 0][lrow] = wv.x; Ws[kq + 1][lrow] = wv.y; Ws[kq + 2][lrow] = wv.z; Ws[kq + 3][lrow] = wv.w;
-    if (SWIGLU) {
-      const float4 w2 = *reinterpret_cast<const float4*>(W2 + (int64_t)wn_ * a.K + k0 + kq);
-      W2s[kq + 0][lrow] = w2.x; W2s[kq + 1][lrow] = w2.y; W2s[kq + 2][lrow] = w2.z; W2s[kq + 3][lrow] = w2.w;
-    }
-    __syncthreads();
+  constexpr int NWT = SWIGLU ? 2 : 1, NF = FM * FN;
+  static_assert(NF % 4 == 0, "each wave finishes NF / 4 fragments");
+  __shared__ f32x4 red[4][NWT][NF][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ntn = (a.N + 16 * FN - 1) / (16 * FN);
+  const int m0 = blockIdx.x / ntn * (16 * FM), n0 = blockIdx.x % ntn * (16 * FN);
+  const int kq = a.K / 4, ko = wave * kq + 4 * (lane >> 4);      // K is a multiple of 64
+  const float* xp[FM];
+  const float* wp[NWT][FN];
 #pragma unroll
-    for (int k = 0; k < TK; ++k) {
-      float xa[4], wb[4];
+  for (int i = 0; i < FM; ++i)
+    xp[i] = (const float*)a.X + (int64_t)min(m0 + 16 * i + (lane & 15), a.M - 1) * a.ldx + ko;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xa[i] = Xs[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wb[j] = Ws[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += xa[i] * wb[j];
-      if (SWIGLU) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) wb[j] = W2s[k][tx * 4 + j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc2[i][j] += xa[i] * wb[j];
-      }
-    }
-    __syncthreads();
+  for (int i = 0; i < FN; ++i) {
+    const int64_t o = (int64_t)min(n0 + 16 * i + (lane & 15), a.N - 1) * a.K + ko;
+    wp[0][i] = (const float*)a.W + o;
+    if (SWIGLU) wp[NWT - 1][i] = (const float*)a.W2 + o;
   }
-
-  if (a.lora.enabled) {
-    const GemmLora& L = a.lora;
-    const float* U = (const float*)L.U;
-    const int mlast = min(m0 + TM, a.M) - 1;
-    const int t0 = L.row_task[m0], t1 = L.row_task[mlast];
-    for (int t = t0; t <= t1; ++t) {
-      const int r = min(L.rank[t], L.max_rank) & ~7;
-      if (r <= 0) continue;
-      const int s0 = L.seg_row[t], s1 = L.seg_row[t + 1];
+  f32x4 acc[NWT][FM][FN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m < s0 || m >= s1 || m >= a.M) continue;
+  for (int w = 0; w < NWT; ++w)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = n0 + tx * 4 + j;
-          if (n >= a.N) continue;
-          const int slot = SWIGLU ? 0 : n / L.slot_width;
-          const int nrow = SWIGLU ? n : n - slot * L.slot_width;
-          if (L.B[slot] != nullptr) {
-            const float* Bt = (const float*)L.B[slot][t];
-            const float* u = U + (int64_t)m * L.ldu + L.ucol[slot];
-            float s = 0.f;
-            for (int q = 0; q < r; ++q) s += u[q] * Bt[(int64_t)nrow * r + q];
-            acc[i][j] += s;
-          }
-          if (SWIGLU && L.B[1] != nullptr) {
-            const float* Bt2 = (const float*)L.B[1][t];
-            const float* u2 = U + (int64_t)m * L.ldu + L.ucol[1];
-            float s2 = 0.f;
-            for (int q = 0; q < r; ++q) s2 += u2[q] * Bt2[(int64_t)nrow * r + q];
-            acc2[i][j] += s2;
-          }
-        }
-      }
-    }
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[w][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 xv[2][FM], wv[2][NWT][FN];
+  auto load = [&](int s, int k) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i) xv[s][i] = *reinterpret_cast<const f32x4*>(xp[i] + k);
+#pragma unroll
+    for (int w = 0; w < NWT; ++w)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) wv[s][w][j] = *reinterpret_cast<const f32x4*>(wp[w][j] + k);
+  };
+  auto step = [&](int s) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int w = 0; w < NWT; ++w)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) acc[w][i][j] = mfma_f32(wv[s][w][j][e], xv[s][i][e], acc[w][i][j]);
+  };
+  load(0, 0);
+  for (int k = 0; k < kq; k += 32) {                  // two 16-column steps, the next one's loads in flight
+    if (k + 16 < kq) load(1, k + 16);
+    step(0);
+    if (k + 32 < kq) load(0, k + 32);
+    if (k + 16 < kq) step(1);
   }
-
-  const float* bias = (const float*)a.bias;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    const int n = n0 + tx * 4;
+  for (int w = 0; w < NWT; ++w)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) red[wave][w][f][lane] = acc[w][f / FN][f % FN];
+  __syncthreads();
+  const GemmLora& L = a.lora;
+#pragma unroll
+  for (int q = 0; q < NF / 4; ++q) {
+    const int f = wave + 4 * q;
+    const int m = m0 + 16 * (f / FN) + (lane & 15), n = n0 + 16 * (f % FN) + 4 * (lane >> 4);
     if (m >= a.M || n >= a.N) continue;
-    float v[4];
+    f32x4 v[NWT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[j] = acc[i][j] + (bias ? bias[n + j] : 0.f);
-      if (SWIGLU) v[j] = silu_exact(acc[i][j]) * acc2[i][j];
-      else if (EPI == EPI_GELU) v[j] = gelu_erf(v[j]);
+    for (int w = 0; w < NWT; ++w) v[w] = ((red[0][w][f][lane] + red[1][w][f][lane]) + red[2][w][f][lane]) + red[3][w][f][lane];
+    if (L.enabled) {
+      const int slot = SWIGLU ? 0 : n / L.slot_width;
+      v[0] += lora_f32(L, slot, m, SWIGLU ? n : n - slot * L.slot_width);
+      if (SWIGLU) v[NWT - 1] += lora_f32(L, 1, m, n);
     }
-    float* dst = (float*)a.out + (int64_t)m * a.ldo + n;
-    if (EPI == EPI_RESID) {
-      float4 o = *reinterpret_cast<float4*>(dst);
-      o.x += v[0]; o.y += v[1]; o.z += v[2]; o.w += v[3];
-      *reinterpret_cast<float4*>(dst) = o;
-    } else {
-      *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    if (a.bias && !SWIGLU) v[0] += *reinterpret_cast<const f32x4*>((const float*)a.bias + n);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (SWIGLU) v[0][e] = silu_exact(v[0][e]) * v[NWT - 1][e];
+      else if (EPI == EPI_GELU) v[0][e] = gelu_erf(v[0][e]);
+    }
+    f32x4* dst = reinterpret_cast<f32x4*>((float*)a.out + (int64_t)m * a.ldo + n);
+    *dst = EPI == EPI_RESID ? *dst + v[0] : v[0];
+  }
+}
+
+// 64x64 tiles where they give every CU a block, else 32x32 (4096 rows x 256
+// columns of K = 1024: 27.5 us against 36.0 with 32x32 tiles; 1024 rows, 64
+// such blocks: 11.5 us with 32x32).  SwiGLU's second weight takes the
+// accumulators of the larger tile, so it stays at 32x32.
+template <int EPI, bool SW>
+void launch_f32(const GemmArgs& a, hipStream_t s) {
+  auto blocks = [&](int b) { return (a.M + b - 1) / b * ((a.N + b - 1) / b); };
+  if constexpr (!SW) {
+    if (blocks(64) >= 256) {
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, SW, 4, 4>), dim3(blocks(64)), dim3(256), 0, s, a);
+      return;
     }
   }
+  hipLaunchKernelGGL((gemm_f32_kernel<EPI, SW, 2, 2>), dim3(blocks(32)), dim3(256), 0, s, a);
 }
 
 // Tile shapes of the large GEMM for an M x N product.  A launch of R tiles
@@ -984,9 +1010,7 @@ hipError_t launch_one(int dtype, const GemmArgs& a0, hipStream_t s) {
     const int grid = ((a.M + BM - 1) / BM) * ((a.N + nt - 1) / nt);
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, SW>), dim3(grid), dim3(256), 0, s, a);
   } else {
-    const GemmArgs& a = a0;
-    const int grid = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI, SW>), dim3(grid), dim3(256), 0, s, a);
+    launch_f32<EPI, SW>(a0, s);
   }
   return hipGetLastError();
 }

@@ -13,7 +13,8 @@
 // bf16: v_mfma_f32_16x16x32_bf16 with operands read straight from global
 // memory (16-byte per-lane loads); the adapter factor feeds the MFMA A slot,
 // the activation rows the B slot, so each lane ends with 4 consecutive
-// output columns of one row.  fp32: plain per-thread dot products.
+// output columns of one row.  fp32: the fp32 MFMA for the shrink, plain dot
+// products elsewhere.
 #include <algorithm>
 
 #include "vfm_internal.h"
@@ -198,94 +199,56 @@ __global__ __launch_bounds__(64 * NWV) void shrink_bf16_kernel(Plan pl, ShrinkAr
   }
 }
 
-// fp32 shrink: one block per (16-row group of a segmented tile, projection);
-// thread (row r, column jj) accumulates U[r, jj + 16 q] for q < rpad / 16
-// over the whole of K with 16-byte loads (the row's loads are shared by its
-// 16 threads through L1).  No LDS, no barrier.
-__global__ __launch_bounds__(256) void shrink_f32_stream_kernel(Plan pl, ShrinkArgs a) {
+// fp32 shrink: one block per (16-row group of a segmented tile, projection),
+// v_mfma_f32_16x16x4_f32 with the task's A rows in the A slot and the 16
+// activation rows in the B slot; the 4 waves each take a quarter of K and
+// their sums are added in wave order, so the chain over K is a quarter as
+// long (latency bound: 1024 rows of width 256, 14.3 us with one thread per
+// (row, column) over all of K, 5.4 us so).  A lane's 16-byte load holds 4
+// consecutive k; MFMA e takes component e of both operands.
+template <int NSUB>
+__global__ __launch_bounds__(256) void shrink_f32_kernel(Plan pl, ShrinkArgs a) {
   __shared__ int tslot;
+  __shared__ f32x4 red[4][NSUB][64];
   const int tile = blockIdx.x >> 2, grp = blockIdx.x & 3, p = blockIdx.y;
   const int t = block_tile_task(pl, tile, &tslot);
   const int r0 = pl.seg_row[t] + (tile - pl.rtile_off[t]) * VFM_ROW_TILE + grp * 16;
   const int r1 = min(pl.seg_row[t] + (tile - pl.rtile_off[t] + 1) * VFM_ROW_TILE, pl.seg_row[t + 1]);
-  if (r0 >= r1) return;
-  const int r = threadIdx.x >> 4, jj = threadIdx.x & 15;
-  const int m = r0 + r;
-  const int rank = min(a.rank[t], a.rpad) & ~7;
-  const int nq = a.rpad / 16;                         // outputs per thread (2 or 4)
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  if (rank > 0 && m < r1) {
-    const float* xr = (const float*)a.X + (int64_t)m * a.ldx;
-    const float* At = (const float*)a.A[p][t];
-    for (int k = 0; k < a.K; k += 4) {
-      const float4 xv = *reinterpret_cast<const float4*>(xr + k);
+  if (r0 >= r1) return;                               // block-uniform
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
+  const int m = r0 + (lane & 15);
+  const int rank = min(a.rank[t], NSUB * 16) & ~7;
+  f32x4 acc[NSUB];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int j = jj + 16 * q;
-        if (q < nq && j < rank) {
-          const float4 av = *reinterpret_cast<const float4*>(At + (int64_t)j * a.K + k);
-          acc[q] = fmaf(xv.x, av.x, acc[q]);
-          acc[q] = fmaf(xv.y, av.y, acc[q]);
-          acc[q] = fmaf(xv.z, av.z, acc[q]);
-          acc[q] = fmaf(xv.w, av.w, acc[q]);
-        }
-      }
-    }
-  }
-  if (m >= r1) return;
-  const float sc = a.scale[t];
-  float* U = (float*)a.U;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (q < nq) U[(int64_t)m * a.ldu + a.ucol[p] + jj + 16 * q] = acc[q] * sc;
-}
-
-__global__ __launch_bounds__(256) void shrink_f32_kernel(Plan pl, ShrinkArgs a) {
-  // One block per (row tile, projection).  K is walked in 32-column chunks
-  // staged in LDS (the tile's rows and the task's A rows); thread (row i,
-  // group g) accumulates rpad/4 outputs of row i from LDS.
-  constexpr int KC = 32;
-  __shared__ float xs[VFM_ROW_TILE][KC + 1];
-  __shared__ float as[VFM_MAX_RANK][KC + 1];
-  int t, r0, r1;
-  tile_rows(pl, blockIdx.x, t, r0, r1);
-  const int p = blockIdx.y;
-  const int rank = min(a.rank[t], a.rpad) & ~7;
-  const float sc = a.scale[t];
-  const float* X = (const float*)a.X;
-  const float* At = rank > 0 ? (const float*)a.A[p][t] : nullptr;
-  float* U = (float*)a.U;
-  const int rows = r1 - r0;
-  const int i = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int jn = a.rpad / 4;                  // outputs per thread (8 or 16)
-  float acc[VFM_MAX_RANK / 4];
-#pragma unroll
-  for (int q = 0; q < VFM_MAX_RANK / 4; ++q) acc[q] = 0.f;
+  for (int s = 0; s < NSUB; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (rank > 0) {
-    for (int k0 = 0; k0 < a.K; k0 += KC) {
-      for (int e = threadIdx.x; e < VFM_ROW_TILE * KC; e += 256) {
-        const int r = e / KC, k = e % KC;
-        xs[r][k] = r < rows ? X[(int64_t)(r0 + r) * a.ldx + k0 + k] : 0.f;
-      }
-      for (int e = threadIdx.x; e < a.rpad * KC; e += 256) {
-        const int j = e / KC, k = e % KC;
-        as[j][k] = j < rank ? At[(int64_t)j * a.K + k0 + k] : 0.f;
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int k = 0; k < KC; ++k) {
-        const float xv = xs[i][k];
+    const int kq = a.K / 4, ko = wave * kq + 4 * g;   // K is a multiple of 64
+    const float* xr = (const float*)a.X + (int64_t)min(m, r1 - 1) * a.ldx + ko;
+    const float* ar[NSUB];
 #pragma unroll
-        for (int q = 0; q < VFM_MAX_RANK / 4; ++q)
-          if (q < jn) acc[q] = fmaf(xv, as[g * jn + q][k], acc[q]);
+    for (int s = 0; s < NSUB; ++s)
+      ar[s] = (const float*)a.A[p][t] + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + ko;
+#pragma unroll 4
+    for (int k = 0; k < kq; k += 16) {
+      const f32x4 xv = *reinterpret_cast<const f32x4*>(xr + k);
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) {
+        f32x4 av = *reinterpret_cast<const f32x4*>(ar[s] + k);
+        if (s * 16 + (lane & 15) >= rank) av = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], xv[e], acc[s], 0, 0, 0);
       }
-      __syncthreads();
     }
   }
-  if (i < rows) {
 #pragma unroll
-    for (int q = 0; q < VFM_MAX_RANK / 4; ++q)
-      if (q < jn) U[(int64_t)(r0 + i) * a.ldu + a.ucol[p] + g * jn + q] = acc[q] * sc;
+  for (int s = 0; s < NSUB; ++s) red[wave][s][lane] = acc[s];
+  __syncthreads();
+  const float sc = a.scale[t];
+  // one sub-tile per wave; the slot's columns past the computed ones are zeros
+  if (m < r1 && wave < a.rpad / 16) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (wave < NSUB) v = (((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane]) * sc;
+    *reinterpret_cast<f32x4*>((float*)a.U + (int64_t)m * a.ldu + a.ucol[p] + wave * 16 + 4 * g) = v;
   }
 }
 
@@ -461,6 +424,9 @@ __global__ __launch_bounds__(64 * HEAD_WAVES) void heads_bf16_kernel(Plan pl, co
   }
 }
 
+// fp32: 16 lanes per (request, output), each lane every 16th group of 4
+// columns, so a block has 16 dots in flight (one thread per dot walked K
+// alone: 40.1 us for 16 requests of 10 outputs, 6.0 us so).
 template <bool HID>
 __global__ __launch_bounds__(256) void heads_f32_kernel(Plan pl, const float* __restrict__ pooled,
                                                         int d, vfm_head_table h, float* __restrict__ hid,
@@ -475,24 +441,37 @@ __global__ __launch_bounds__(256) void heads_f32_kernel(Plan pl, const float* __
   const float* Wt = (const float*)(HID ? h.W1[t] : h.W[t]);
   const float* bt = HID ? (h.b1 ? (const float*)h.b1[t] : nullptr) : (h.b ? (const float*)h.b[t] : nullptr);
   const bool from_hid = !HID && mlp;
-  const int K = from_hid ? h.hidden : d;
+  const int K = from_hid ? h.hidden : d;              // a multiple of 64
   const float* in = from_hid ? hid : pooled;
-  for (int e = threadIdx.x; e < (p1 - p0) * 64; e += 256) {
-    const int p = p0 + e / 64, n = n0 + e % 64;
-    if (n >= n_out) continue;
-    float s = bt ? bt[n] : 0.f;
-    for (int k = 0; k < K; ++k) s += in[(int64_t)p * K + k] * Wt[(int64_t)n * K + k];
+  const int sub = threadIdx.x & 15, nc = min(64, n_out - n0);
+  const int total = (p1 - p0) * nc;
+  for (int e0 = 0; e0 < total; e0 += 16) {
+    const int e = min(e0 + (int)(threadIdx.x >> 4), total - 1);   // the last ones again past the end
+    const int p = p0 + e / nc, n = n0 + e % nc;
+    const float* x = in + (int64_t)p * K + 4 * sub;
+    const float* w = Wt + (int64_t)n * K + 4 * sub;
+    float s = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < K; k += 64) {
+      const float4 xv = *reinterpret_cast<const float4*>(x + k), wv = *reinterpret_cast<const float4*>(w + k);
+      s = fmaf(xv.x, wv.x, s);
+      s = fmaf(xv.y, wv.y, s);
+      s = fmaf(xv.z, wv.z, s);
+      s = fmaf(xv.w, wv.w, s);
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, 64);
+    if (sub != 0 || e0 + (int)(threadIdx.x >> 4) >= total) continue;
+    s += bt ? bt[n] : 0.f;
     if (HID) {
       hid[(int64_t)p * h.hidden + n] =
           h.act == VFM_ACT_RELU ? fmaxf(s, 0.f) : 0.5f * s * (1.f + erff(s * 0.70710678118654752440f));
     } else {
       const int req = pl.order[p];
-      if (n >= min(n_out, pl.out_off[req + 1] - pl.out_off[req])) continue;
-      out[pl.out_off[req] + n] = s;
+      if (n < min(n_out, pl.out_off[req + 1] - pl.out_off[req])) out[pl.out_off[req] + n] = s;
     }
   }
 }
-
 
 // ---------------------------------------------------------------------------
 // Greedy token selection: one block per request (original order), each
@@ -555,12 +534,11 @@ hipError_t launch_lora_shrink(int dtype, const Plan& pl, const ShrinkArgs& a, hi
     else SHR_NP(4);
 #undef SHR_NP
 #undef SHR
-  } else if (a.K % 4 == 0) {
-    dim3 grid(4 * pl.n_rtiles, a.n_proj);
-    hipLaunchKernelGGL(shrink_f32_stream_kernel, grid, dim3(256), 0, s, pl, a);
   } else {
-    dim3 grid(pl.n_rtiles, a.n_proj);
-    hipLaunchKernelGGL(shrink_f32_kernel, grid, dim3(256), 0, s, pl, a);
+    dim3 grid(4 * pl.n_rtiles, a.n_proj);
+    if (a.nsub <= 1) hipLaunchKernelGGL(shrink_f32_kernel<1>, grid, dim3(256), 0, s, pl, a);
+    else if (a.nsub == 2) hipLaunchKernelGGL(shrink_f32_kernel<2>, grid, dim3(256), 0, s, pl, a);
+    else hipLaunchKernelGGL(shrink_f32_kernel<4>, grid, dim3(256), 0, s, pl, a);
   }
   return hipGetLastError();
 }

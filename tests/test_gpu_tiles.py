@@ -9,8 +9,8 @@ from oracle import vfm_oracle as O
 from paper_2606_09643_amd import binding as B
 from paper_2606_09643_amd import runner as R
 from paper_2606_09643_amd import workloads as wl
-from tests.gpu_common import log, oracle_plan, seeded_rows, set_rows, tol
-from tests.helpers import np64, spec_of
+from tests.gpu_common import log, oracle_layer_rows, oracle_plan, seeded_rows, set_rows, tol
+from tests.helpers import np64, oracle_weights, spec_of
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +59,46 @@ def test_heads_output_and_request_remainders(idx, d, pool, hidden):
     err = np.abs(got - ref).max() / np.abs(ref).max()
     log(f"  max rel err {err:.3e}")
     assert err < tol(w)
+
+
+def _layer_case(w, task, length, ranks, seed=1, b_std=0.05):
+    batch = wl.Batch(np.asarray(task, np.int32), np.asarray(length, np.int32), None)
+    model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=b_std, seed=seed)
+    pb = R.make_batch(w, batch, None)
+    rows = seeded_rows(pb.T, w.d, 7)
+    x = torch.empty(pb.T, w.d, device="cuda")
+    ws = torch.empty(B.vfm_workspace_size(model.cfg, pb.c, model.lora_c(0)), dtype=torch.uint8, device="cuda")
+    pl = oracle_plan(w, batch)
+
+    def run(x):
+        set_rows(x, rows)
+        B.vfm_layer_forward(model.cfg, model.c_layers[0], model.lora_c(0), pb.c, x, workspace=ws)
+        return x.double().cpu().numpy()
+
+    return model, pl, rows, run(x)
+
+
+def _check_layer(w, model, pl, rows, got, reqs):
+    ref = oracle_layer_rows(w, oracle_weights(model.layers[0]), model.adapters[0], pl, rows, reqs)
+    cu, worst = pl["cu_seqlens"], 0.0
+    for p in reqs:
+        worst = max(worst, O.row_rel_error(got[int(cu[p]):int(cu[p + 1])], ref[p][0]))
+    log(f"  max rel err {worst:.3e}")
+    assert worst < tol(w)
+
+
+@pytest.mark.parametrize("lens,family,hd,d_ff", [
+    ([1], "encoder", 64, 64), ([31, 1, 2], "encoder", 64, 320), ([33, 64, 65], "encoder", 128, 1024),
+    ([200, 16, 17, 1], "encoder", 64, 2048), ([130, 7, 64], "decoder", 128, 192),
+    ([1100, 400, 700, 2000, 5], "encoder", 64, 1024)])
+def test_f32_layer_tiles(lens, family, hd, d_ff):
+    """The fp32 layer at the edges of its 32- and 64-row tiles, 16-query
+    attention groups and 16 / 32 / 64-rank shrink sub-tiles (both GEMM tile
+    shapes; the last batch takes the 64x64 one), d_ff not a multiple of 128."""
+    w = wl.WORKLOADS[1].replace(family=family, n_heads=256 // hd, head_dim=hd, d_ff=d_ff, n_tasks=5,
+                                lora_targets=("q", "v", "o", "gate", "up", "down") if family == "decoder"
+                                else ("q", "k", "o", "up", "down"))
+    log(f"f32 {family} lens={lens} hd={hd} f={d_ff}")
+    task = [4, 1, 0, 3, 1][:len(lens)]
+    out = _layer_case(w, task, lens, [8, 64, 0, 32, 16])
+    _check_layer(w, out[0], out[1], out[2], out[3], range(len(lens)))
