@@ -35,10 +35,11 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 // kc ^ ((r >> 1) & 7), which spreads the 16-row fragment reads over all banks.
 __device__ __forceinline__ int swz(int row, int kc) { return kc ^ ((row >> 1) & 7); }
 
-constexpr int SBM = 256, SBK = 64;
+constexpr int SBK = 64;
 
 // ---------------------------------------------------------------------------
-// Split-K GEMM, BN = 64 * NWN columns per block, 4 x NWN waves of 64 x 64.
+// Split-K GEMM, BM rows x BN = 64 * NWN columns per block, 4 x NWN waves of
+// BM / 4 x 64.
 //
 // Every weight element is used by the few hundred rows of one tile only, so
 // the weight stream comes from HBM at full latency while the activation
@@ -48,6 +49,15 @@ constexpr int SBM = 256, SBK = 64;
 // keeping the two streams in different waves lets the short-latency
 // activation loads be waited on without waiting for the weight loads
 // behind them.  All waves take part in the MFMA work.
+//
+// BM is 64, 128 or 256, the smallest that holds the batch (256-row tiles
+// beyond): a tile's rows past the batch cost their LDS fill and their MFMAs
+// like real ones, and a 256-row tile of one row spends more on them than on
+// the weights.  One row of the 7B decoder, QKV / O / gate+up / down: 27.4 /
+// 12.3 / 47.2 / 28.0 us with 256-row tiles, 18.7 / 8.9 / 29.6 / 20.8 with 64
+// (5.4 / 3.8 / 6.1 / 4.3 TB/s of weights); deeper weight rings in the LDS that
+// this frees (6 or 8 stages) gained nothing.  The K steps and their order are
+// the same for every BM, and so are a row's sums.
 // ---------------------------------------------------------------------------
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -55,14 +65,14 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);   // vmcnt(N), lgkmcnt / expcnt not waited
 }
 
-template <int NWN, int WST>
+template <int BM, int NWN, int WST>
 __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   // loader waves: half for each operand, except 192 columns (12 waves), whose
-  // 256 activation rows need a power-of-two share (8 activation, 4 weight)
-  constexpr int BN = 64 * NWN, NW = 4 * NWN, XW = NWN == 3 ? 8 : NW / 2, WW = NW - XW;
-  constexpr int SA = SBM * SBK, SB = BN * SBK;
-  constexpr int XR = SBM / (8 * XW), WR = BN / (8 * WW);    // 1 KB rounds per stage and loader wave
-  static_assert(XR * 8 * XW == SBM && WR * 8 * WW == BN, "loader rounds");
+  // activation rows need a power-of-two share (8 activation, 4 weight)
+  constexpr int BN = 64 * NWN, FM = BM / 64, NW = 4 * NWN, XW = NWN == 3 ? 8 : NW / 2, WW = NW - XW;
+  constexpr int SA = BM * SBK, SB = BN * SBK;
+  constexpr int XR = BM / (8 * XW), WR = BN / (8 * WW);    // 1 KB rounds per stage and loader wave
+  static_assert(XR * 8 * XW == BM && WR * 8 * WW == BN, "loader rounds");
   static_assert(WST == 3 || WST == 4, "weight stages");
   static_assert(WR * (WST - 2) < 16, "vmcnt range");
   __shared__ __attribute__((aligned(16))) bf16 smem[2 * SA + WST * SB];
@@ -77,7 +87,7 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   const int bx = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (bx >= ntn * a.nsplit) return;
   const int tn = bx % ntn, split = bx / ntn;
-  const int m0 = blockIdx.y * SBM, n0 = tn * BN;
+  const int m0 = blockIdx.y * BM, n0 = tn * BN;
   const int nkt = a.K / SBK;
   const int kt0 = (int)((int64_t)split * nkt / a.nsplit);
   const int kt1 = (int)((int64_t)(split + 1) * nkt / a.nsplit);
@@ -121,9 +131,9 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
                                        (lptr_t)(Ws + slot * SB + (i * WW + lw) * 512), 16, 0, 2);
   };
 
-  f32x4 acc[4][4];
+  f32x4 acc[FM][4];
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi)
+  for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
     for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (nk > 0) {
@@ -163,19 +173,19 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
         const int kc = kk * 4 + (lane >> 4);
-        bf16x8 wf[4], xf[4];
+        bf16x8 wf[4], xf[FM];
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni) {
           const int r = wn * 64 + ni * 16 + (lane & 15);
           wf[ni] = *reinterpret_cast<const bf16x8*>(Bs + r * SBK + swz(r, kc) * 8);
         }
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
-          const int r = wm * 64 + mi * 16 + (lane & 15);
+        for (int mi = 0; mi < FM; ++mi) {
+          const int r = wm * 16 * FM + mi * 16 + (lane & 15);
           xf[mi] = *reinterpret_cast<const bf16x8*>(As + r * SBK + swz(r, kc) * 8);
         }
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
           for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = mfma16(wf[ni], xf[mi], acc[mi][ni]);
       }
@@ -185,8 +195,8 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   // lane holds D[n = 4 * (lane >> 4) + i][m = lane & 15] of each 16 x 16 block
   float* Zs = a.Z + (int64_t)split * a.M * a.N;
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi) {
-    const int m = m0 + wm * 64 + mi * 16 + (lane & 15);
+  for (int mi = 0; mi < FM; ++mi) {
+    const int m = m0 + wm * 16 * FM + mi * 16 + (lane & 15);
     if (m >= a.M) continue;
 #pragma unroll
     for (int ni = 0; ni < 4; ++ni) {
@@ -410,13 +420,18 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& a0, hipStream_t s) {
   int bn;
   skinny_shape(a.N, a.K, &bn, &a.nsplit);
   const int ntn = (a.N + bn - 1) / bn;
-  dim3 grid((ntn * a.nsplit + 7) & ~7, (a.M + SBM - 1) / SBM);
-  if (bn == 128)
-    hipLaunchKernelGGL((gemm_skinny_kernel<2, 4>), grid, dim3(512), 0, s, a);
-  else if (bn == 192)
-    hipLaunchKernelGGL((gemm_skinny_kernel<3, 4>), grid, dim3(768), 0, s, a);
-  else
-    hipLaunchKernelGGL((gemm_skinny_kernel<4, 3>), grid, dim3(1024), 0, s, a);
+  const int bm = a.M <= 64 ? 64 : a.M <= 128 ? 128 : 256;
+  dim3 grid((ntn * a.nsplit + 7) & ~7, (a.M + bm - 1) / bm);
+#define VFM_SK(BM_)                                                                                         \
+  do {                                                                                                      \
+    if (bn == 128) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 2, 4>), grid, dim3(512), 0, s, a);           \
+    else if (bn == 192) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 3, 4>), grid, dim3(768), 0, s, a);      \
+    else hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 4, 3>), grid, dim3(1024), 0, s, a);                    \
+  } while (0)
+  if (bm == 64) VFM_SK(64);
+  else if (bm == 128) VFM_SK(128);
+  else VFM_SK(256);
+#undef VFM_SK
   return hipGetLastError();
 }
 
