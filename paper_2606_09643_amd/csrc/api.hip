@@ -382,7 +382,9 @@ int layer_impl(const vfm_cfg& c, const vfm_layer_weights* w, const vfm_lora_tabl
     fused_norm = false;
     bool any = false;
     for (int p : projs) any = any || has(p);
-    if (!skinny) {
+    // (with RoPE, the QKV projection of a small batch stays on the split path,
+    // whose finalize rotates before the one rounding to bf16)
+    if (!skinny || (K <= VFM_DIRECT_K && !fin_rope.on)) {
       if (any) {
         ShrinkArgs a = {};
         a.X = X; a.ldx = K; a.K = K; a.U = U; a.ldu = ldu; a.rpad = rpad;

@@ -23,6 +23,7 @@
 //
 // fp32 path: fp32 MFMA with small tiles and K split over a block's waves
 // (gemm_f32_kernel), the same epilogues.
+#include <algorithm>
 #include <type_traits>
 
 #include "vfm_internal.h"
@@ -200,17 +201,17 @@ __device__ __forceinline__ int lds_chunk(int r, int q) {
   return q ^ (r & S);
 }
 
-template <int EPI, bool SWIGLU, int BMT, int BNT, int FM, int FN>
+template <int EPI, bool SWIGLU, int BMT, int BNT, int WM, int NST, int FM, int FN>
 __device__ __forceinline__ void epilogue_lds(const GemmArgs& a, char* lds, int m0, int n0, int wm, int wn,
-                                             int lane, int tid, const f32x4 (&acc)[FM][FN]) {
-  constexpr int NTH = 512, TM = BMT / 4, TN = BNT / 2;
+                                             int lane, int tid, const f32x4 (&acc)[FM][FN], const float4* old) {
+  constexpr int NTH = 128 * WM, TM = BMT / WM, TN = BNT / 2;
   constexpr int NC = SWIGLU ? BNT / 2 : BNT;        // output columns of the tile
   const int g = lane >> 4;
   __syncthreads();                                  // every wave is done with the operand stages
   if (EPI != EPI_RESID) {
     constexpr int QR = NC / 8;                      // 16-byte chunks per row (bf16)
     static_assert(QR % 4 == 0, "row chunks");
-    static_assert(BMT * NC * 2 <= 2 * (BMT + BNT) * BK * 2, "tile fits the operand LDS");
+    static_assert(BMT * NC * 2 <= NST * (BMT + BNT) * BK * 2, "tile fits the operand LDS");
     bf16* T = reinterpret_cast<bf16*>(lds);
     if (SWIGLU) {
 #pragma unroll
@@ -306,13 +307,13 @@ __device__ __forceinline__ void epilogue_lds(const GemmArgs& a, char* lds, int m
   constexpr int HR = BMT / 2;                       // rows per half
   constexpr int QR = NC / 4;                        // 16-byte chunks per row (fp32)
   static_assert(QR % 4 == 0, "row chunks");
-  static_assert(HR * NC * 4 <= 2 * (BMT + BNT) * BK * 2, "half tile fits the operand LDS");
+  static_assert(HR * NC * 4 <= NST * (BMT + BNT) * BK * 2, "half tile fits the operand LDS");
   float* T = reinterpret_cast<float*>(lds);
   const bf16* bias = (const bf16*)a.bias;
   float* x = (float*)a.out;
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
-    if ((wm >> 1) == half) {                        // waves wm = 2 half, 2 half + 1 own these rows
+    if (wm / (WM / 2) == half) {                    // these waves own the half's rows
 #pragma unroll
       for (int ni = 0; ni < FN; ++ni) {
         const int j = wn * TN + ni * 16 + 4 * g;
@@ -324,7 +325,7 @@ __device__ __forceinline__ void epilogue_lds(const GemmArgs& a, char* lds, int m
         }
 #pragma unroll
         for (int mi = 0; mi < FM; ++mi) {
-          const int r = (wm & 1) * TM + mi * 16 + (lane & 15);   // row within the half
+          const int r = wm % (WM / 2) * TM + mi * 16 + (lane & 15);   // row within the half
           const float4 o = make_float4(acc[mi][ni][0] + bv[0], acc[mi][ni][1] + bv[1],
                                        acc[mi][ni][2] + bv[2], acc[mi][ni][3] + bv[3]);
           *reinterpret_cast<float4*>(T + r * NC + lds_chunk<QR>(r, j >> 2) * 4) = o;
@@ -332,14 +333,16 @@ __device__ __forceinline__ void epilogue_lds(const GemmArgs& a, char* lds, int m
       }
     }
     __syncthreads();
-#pragma unroll 4
+#pragma unroll (WM == 2 ? HR * QR / NTH : 4)
     for (int e = tid; e < HR * QR; e += NTH) {
       const int r = e / QR, q = e % QR;
       const int m = m0 + half * HR + r, n = n0 + q * 4;
       if (m < a.M && n < a.N) {
         const float4 v = *reinterpret_cast<const float4*>(T + r * NC + lds_chunk<QR>(r, q) * 4);
         float4* dst = reinterpret_cast<float4*>(x + (int64_t)m * a.ldo + n);
-        float4 o = *dst;
+        float4 o;
+        if constexpr (WM == 2) o = old[(half * HR * QR + e - tid) / NTH];
+        else o = *dst;
         o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
         *dst = o;
       }
@@ -370,14 +373,30 @@ __device__ __forceinline__ void epilogue_lds(const GemmArgs& a, char* lds, int m
 constexpr int LGM = 4;
 
 
-template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK>
-__global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
-  constexpr int NW = 8, NTH = 512, WN = 2, TM = BMT / 4, TN = BNT / 2, FM = TM / 16, FN = TN / 16;
+// wait until at most `later` steps of ND loads each are outstanding (MAX at
+// most), and for this wave's LDS accesses
+template <int ND, int MAX>
+__device__ __forceinline__ void wait_steps(int later) {
+  static_assert(ND * MAX < 64, "vmcnt field");
+  if constexpr (MAX == 0) {
+    __builtin_amdgcn_s_waitcnt(0x0070);
+  } else {
+    // vmcnt(MAX ND) (bits 3:0 and 15:14), lgkmcnt(0)
+    if (later >= MAX) __builtin_amdgcn_s_waitcnt(0x0070 | (MAX * ND & 15) | ((MAX * ND >> 4) << 14));
+    else wait_steps<ND, MAX - 1>(later);
+  }
+}
+
+// One output tile, WM x 2 waves, NST LDS stages.
+template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK, int WM, int NST>
+__device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& a) {
+  constexpr int NW = 2 * WM, NTH = 64 * NW, WN = 2, TM = BMT / WM, TN = BNT / 2, FM = TM / 16, FN = TN / 16;
   constexpr int ACH = BMT * 8 / NTH, BCH = BNT * 8 / NTH;  // 16-byte chunks per lane and stage
   constexpr int SA = BMT * BK, SB = BNT * BK;
+  constexpr bool EARLY = WM == 2;                            // small tiles: latency bound
   static_assert(BMT % 64 == 0 && BNT % 64 == 0 && FN % 2 == 0, "tile shape");
-  constexpr int RSTEP = NTH / 8;                             // 64 rows per chunk step
-  __shared__ __attribute__((aligned(16))) bf16 smem[2 * (SA + SB)];
+  constexpr int RSTEP = NTH / 8;                             // rows per chunk step
+  __shared__ __attribute__((aligned(16))) bf16 smem[NST * (SA + SB)];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   constexpr int NTILE = SWIGLU ? BNT / 2 : BNT;  // output columns per block
@@ -527,8 +546,10 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
 #pragma unroll
     for (int ni = 0; ni < FN; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto issue_bb = [&](int e) {
-    bf16* As = smem + (e & 1) * (SA + SB);
+  // LDS stage of step e: e & 1 with two, else the caller's j = e % NST
+  auto stage = [&](int e, int j) -> bf16* { return smem + (NST == 2 ? (e & 1) : j) * (SA + SB); };
+  auto issue_bb = [&](int e, int j) {
+    bf16* As = stage(e, j);
     bf16* Bs = As + SA;
     const int k0 = e * BK;
 #pragma unroll
@@ -547,7 +568,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
     else *reinterpret_cast<bf16x8*>(dst + lane * 8) = bf16x8{};
   };
   auto issue = [&](int e) {
-    bf16* As = smem + (e & 1) * (SA + SB);
+    bf16* As = stage(e, e % NST);
     bf16* Bs = As + SA;
     if (e < nk) {
       const int k0 = e * BK;
@@ -561,7 +582,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
       return;
     }
     const int step = e - nk, part = step % parts;
-    load_step(part);
+    if (!(EARLY && step == 0)) load_step(part);
     const bf16* U = (const bf16*)L.U;
     // this lane's chunk: projection (SwiGLU: gate or up) and chunk within it
     int proj = 0, qq = q;
@@ -599,8 +620,8 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
       if (!skip) dma_or_zero(src != nullptr, src, Bs + (i * NW + wave) * 512);
     }
   };
-  auto compute = [&](int e, bool first_half_only) {
-    const bf16* As = smem + (e & 1) * (SA + SB);
+  auto compute = [&](int e, int j, bool first_half_only) {
+    const bf16* As = stage(e, j);
     const bf16* Bs = As + SA;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
@@ -628,9 +649,28 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
   // The backbone K steps run in a loop of their own (its loads are plain
   // strided tiles), then the LoRA steps; the loop that mixes both kinds of
   // issue costs the backbone loop about a tenth of its speed.
-  issue_bb(0);
-  __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): step 0 and the tile's row tasks
-  __builtin_amdgcn_s_barrier();
+  // the residual values this thread adds in the epilogue (its staging order),
+  // so that small tiles do not wait for them at the end
+  constexpr int NOLD = EPI == EPI_RESID && EARLY ? BMT * BNT / 4 / NTH : 1;
+  float4 old[NOLD];
+  if constexpr (EPI == EPI_RESID && EARLY) {
+    constexpr int QR = BNT / 4;
+#pragma unroll
+    for (int i = 0; i < NOLD; ++i) {
+      const int e = tid + NTH * i, m = m0 + e / QR, n = n0 + e % QR * 4;
+      old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (m < a.M && n < a.N) old[i] = *reinterpret_cast<const float4*>((const float*)a.out + (int64_t)m * a.ldo + n);
+    }
+  }
+  issue_bb(0, 0);
+  if constexpr (NST == 2) {
+    __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): step 0 and the tile's row tasks
+    __builtin_amdgcn_s_barrier();
+  } else {
+#pragma unroll
+    for (int e = 1; e < NST - 1; ++e)
+      if (e < nk) issue_bb(e, e);
+  }
   if (live) {
     int prev = __shfl_up(rt[RPL - 1], 1, 64);
     if (lane == 0) prev = -1;
@@ -644,18 +684,43 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
     for (int j = 0; j < RPL; ++j) nruns += __builtin_popcountll(rstart[j]);
     nlora = (nruns + P - 1) / P * parts;
     nsteps = nk + nlora;
+    if (EARLY) load_step(0);           // the first LoRA step's rank and B pointer arrive during the K loop
   }
-  if (nk < 2) __builtin_amdgcn_s_waitcnt(0xF70);   // no backbone step covers them
-  for (int e = 0; e + 1 < nk; ++e) {
-    issue_bb(e + 1);                   // the other stage: every wave left it at the last barrier
-    compute(e, false);
-    __builtin_amdgcn_s_waitcnt(0xF70);
+  if constexpr (NST == 2) {
+    if (nk < 2) __builtin_amdgcn_s_waitcnt(0xF70);   // no backbone step covers them
+    // (small tiles also wait for their fragment reads before the barrier: what
+    // the compiler leaves of a step's reads until after it would race with
+    // the zeros that the first LoRA step writes, its tables already there;
+    // the large tiles' next write to the stage is a load's round trip away)
+    for (int e = 0; e + 1 < nk; ++e) {
+      issue_bb(e + 1, 0);     // the other stage: every wave left it at the last barrier
+      compute(e, 0, false);
+      __builtin_amdgcn_s_waitcnt(EARLY ? 0x0070 : 0xF70);
+      __builtin_amdgcn_s_barrier();
+    }
+  } else {
+    // NST - 1 steps in flight: step e has landed once at most NST - 2 later
+    // ones are outstanding; the barrier also frees the stage of step e - 1.
+    // The stages are constants of the unrolled loop, so the compiler can tell
+    // the one being read from those being filled.
+    for (int e0 = 0; e0 + 1 < nk; e0 += NST) {
+#pragma unroll
+      for (int j = 0; j < NST; ++j) {
+        const int e = e0 + j;
+        if (e + 1 >= nk) break;
+        wait_steps<ACH + BCH, NST - 2>(nk - 1 - e);
+        __builtin_amdgcn_s_barrier();
+        if (e + NST - 1 < nk) issue_bb(e + NST - 1, (j + NST - 1) % NST);
+        compute(e, j, false);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);  // step nk - 1 and the row tasks
     __builtin_amdgcn_s_barrier();
   }
   bool half_cur = false;                           // step e fills only its first 32 columns
   for (int e = nk - 1; e < nsteps; ++e) {
     if (e + 1 < nsteps) issue(e + 1);
-    compute(e, e >= nk && half_cur);
+    compute(e, e % NST, e >= nk && half_cur);
     half_cur = half_next;
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): DMA and zero writes done
     __builtin_amdgcn_s_barrier();
@@ -664,15 +729,35 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
   // fp32 residual of tiles narrower than 256 columns; the 256-column
   // residual tile writes from registers (its staged form spills)
   if (EPI != EPI_RESID || BNT < 256)
-    epilogue_lds<EPI, SWIGLU, BMT, BNT, FM, FN>(a, reinterpret_cast<char*>(smem), m0, n0, wm, wn, lane, tid,
-                                                 acc);
+    epilogue_lds<EPI, SWIGLU, BMT, BNT, WM, NST, FM, FN>(a, reinterpret_cast<char*>(smem), m0, n0, wm, wn, lane, tid,
+                                                         acc, old);
   else
     epilogue_frags<EPI, SWIGLU, FM, FN>(a, m0 + wm * TM, n0, wn * TN, lane, acc);
 }
 
+template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK>
+__global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
+  gemm_bf16_tile<EPI, SWIGLU, BMT, BNT, PACK, 4, 2>(a);
+}
+
+// The same tile for products with too few 256-row tiles to fill the chip: 4
+// waves, 64 x 64 outputs with 4 LDS stages (64 KB, 2 blocks per CU) or 128 x
+// 64 with 2 (48 KB, 3 blocks per CU).  A 256-row tile is fed at ~25 bytes per
+// clock and CU and idles the matrix units through its first loads and its
+// stores; small tiles move more operand bytes per output but cover more CUs
+// and overlap one block's stores with another's K loop.  1518 x 1024 outputs
+// (48 tiles of 256 x 128): 24.7 -> 12.2 us at K = 1024, 49.0 -> 22.3 at K =
+// 2816; 4728 x 768 at K = 3072: 55.4 -> 40.5.  More stages for 128 x 64 (3: 2
+// blocks per CU), fewer for 64 x 64, and 64 x 128 or 128 x 128 tiles were
+// slower or equal.  K steps and their order are those of the large tiles.
+template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_mid_kernel(GemmArgs a) {
+  gemm_bf16_tile<EPI, SWIGLU, BMT, BNT, PACK, 2, BMT == 64 ? 4 : 2>(a);
+}
+
 // ---------------------------------------------------------------------------
-// Small-M bf16 GEMM (decode-sized batches): 128x128x64, 4 waves of 64x64,
-// register-staged LDS double buffer, more blocks for few rows.
+// bf16 GEMM with 64-bit offsets (operands of 2^31 elements or more): 128x128x64,
+// 4 waves of 64x64, register-staged LDS double buffer.
 // ---------------------------------------------------------------------------
 template <int EPI, bool SWIGLU>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs a) {
@@ -968,6 +1053,27 @@ inline LargePlan large_plan(int M, int N, bool sw, int lora_slot_width, int rope
   return best;
 }
 
+// Estimated time (us) of the plan above and of one launch of bm x 64 mid
+// tiles.  A tile's K step costs its (bm + bn) operand rows of 128 B at the 47
+// GB/s each CU is fed with (2.7 ns a row); to that a 256-row tile adds its
+// first loads and its stores, 7 us per 128 columns, in every round, while the
+// mid tiles share a CU and overlap theirs but once.  Fitted on products of
+// 1182 to 8700 rows, 768 to 4224 columns and K = 768 to 3072.
+inline double large_time(const LargePlan& p, int M, int N, int K, bool sw) {
+  auto one = [&](int rows, const LargeShape& c) {
+    if (rows <= 0) return 0.0;
+    const int nt = sw ? c.bn / 2 : c.bn;
+    const long tiles = (long)((rows + c.bm - 1) / c.bm) * ((N + nt - 1) / nt);
+    return (tiles + 255) / 256 * (K / BK * (c.bm + c.bn) * 0.0027 + 7.0 * c.bn / 128);
+  };
+  return one(p.m1, p.main) + one(M - p.m1, p.tail);
+}
+inline double mid_time(int M, int N, int K, bool sw, int bm) {
+  const int nt = sw ? 32 : 64;
+  const double per_cu = (double)((M + bm - 1) / bm) * ((N + nt - 1) / nt) / 256.0;
+  return (per_cu < 1.0 ? 1.0 : per_cu) * (K / BK) * (bm + 64) * 0.0024 + 4.0;
+}
+
 template <int EPI, bool SW, int BMT, int BNT>
 void launch_large(const GemmArgs& a, hipStream_t s) {
   const int nt = SW ? BNT / 2 : BNT;
@@ -986,13 +1092,40 @@ void launch_large_shape(const GemmArgs& a, const LargeShape& sh, hipStream_t s) 
   else launch_large<EPI, SW, 256, 128>(a, s);
 }
 
+template <int EPI, bool SW, int BMT>
+void launch_mid(const GemmArgs& a, hipStream_t s) {
+  const int nt = SW ? 32 : 64;
+  const int ntiles = ((a.M + BMT - 1) / BMT) * ((a.N + nt - 1) / nt);
+  const int grid = (ntiles + 7) / 8 * 8;
+  if (a.lora.enabled && a.lora.max_rank <= 16)
+    hipLaunchKernelGGL((gemm_bf16_mid_kernel<EPI, SW, BMT, 64, true>), dim3(grid), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_bf16_mid_kernel<EPI, SW, BMT, 64, false>), dim3(grid), dim3(256), 0, s, a);
+}
+
 template <int EPI, bool SW>
 hipError_t launch_one(int dtype, const GemmArgs& a0, hipStream_t s) {
-  // the fused rotary embedding needs whole heads in a tile
-  const LargePlan pl = large_plan(a0.M, a0.N, SW, a0.lora.enabled ? a0.lora.slot_width : 0,
-                                  a0.rope.on ? a0.rope.head_dim : 0);
+  if (dtype != VFM_BF16) {
+    if (a0.rope.on) return hipErrorInvalidValue;
+    launch_f32<EPI, SW>(a0, s);
+    return hipGetLastError();
+  }
+  // 32-bit element offsets inside a tile
   const bool fits32 = (int64_t)a0.M * a0.ldx < ((int64_t)1 << 31) && (int64_t)a0.N * a0.K < ((int64_t)1 << 31);
-  if (dtype == VFM_BF16 && a0.M >= 1024 && pl.main.bm > 0 && fits32) {
+  const int slot = a0.lora.enabled && !SW ? a0.lora.slot_width : 0;
+  // the fused rotary embedding needs whole heads in a tile
+  const int rope_hd = a0.rope.on ? a0.rope.head_dim : 0;
+  const LargePlan pl = large_plan(a0.M, a0.N, SW, slot, rope_hd);
+  const bool large_ok = fits32 && pl.main.bm > 0 && a0.M >= 1024;
+  const bool mid_ok = fits32 && slot % 64 == 0 && (rope_hd == 0 || rope_hd == 64);
+  const double t64 = mid_time(a0.M, a0.N, a0.K, SW, 64), t128 = mid_time(a0.M, a0.N, a0.K, SW, 128);
+  if (mid_ok && (!large_ok || std::min(t64, t128) < large_time(pl, a0.M, a0.N, a0.K, SW))) {
+    GemmArgs a = a0;
+    a.m_lo = 0;
+    a.m_hi = a.M;
+    if (t64 <= t128) launch_mid<EPI, SW, 64>(a, s);
+    else launch_mid<EPI, SW, 128>(a, s);
+  } else if (large_ok) {
     GemmArgs a = a0;
     a.m_lo = 0;
     a.m_hi = pl.m1;
@@ -1003,14 +1136,12 @@ hipError_t launch_one(int dtype, const GemmArgs& a0, hipStream_t s) {
       launch_large_shape<EPI, SW>(a, pl.tail, s);
     }
   } else if (a0.rope.on) {
-    return hipErrorInvalidValue;   // only the large-tile kernel applies the rotary embedding
-  } else if (dtype == VFM_BF16) {
+    return hipErrorInvalidValue;   // only the tile kernels apply the rotary embedding
+  } else {
     const GemmArgs& a = a0;
     const int nt = SW ? BN / 2 : BN;
     const int grid = ((a.M + BM - 1) / BM) * ((a.N + nt - 1) / nt);
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, SW>), dim3(grid), dim3(256), 0, s, a);
-  } else {
-    launch_f32<EPI, SW>(a0, s);
   }
   return hipGetLastError();
 }

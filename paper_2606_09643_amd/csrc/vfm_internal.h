@@ -263,6 +263,15 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 
+// Small bf16 batches: projections whose weight has K of at most this many
+// columns skip the split-K path (split GEMM into fp32 partials, split shrink,
+// finalize) for the shrink and one launch of launch_gemm's tiles, whose K loop
+// is then at most 16 steps: the partials' traffic and the finalize launch cost
+// more than the K split saves (197 rows, K = 768, shrink to result: QKV 30.8
+// -> 16.7 us, O with the norm 24.9 -> 18.7, up 24.1 -> 8.2).  The rule looks
+// at the weight alone, so a row's sums do not depend on the batch.
+constexpr int VFM_DIRECT_K = 1024;
+
 // ---- small-batch (decode) projections, bf16 only -------------------------
 // Split-K shared GEMM into fp32 partials: Z[s, m, n] = sum over the s-th
 // K range of X[m, k] W[n, k]; rows n >= n_half of the stacked weight come

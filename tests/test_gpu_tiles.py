@@ -61,6 +61,54 @@ def test_heads_output_and_request_remainders(idx, d, pool, hidden):
     assert err < tol(w)
 
 
+def _rows_of(w, model, task, length, seeds):
+    """Layer outputs of requests whose input rows follow from their own seeds,
+    in arrival order (one list entry per request)."""
+    task, length = np.asarray(task, np.int32), np.asarray(length, np.int32)
+    pb = R.make_batch(w, wl.Batch(task, length, None), None)
+    order = np.argsort(task, kind="stable")
+    x = torch.empty(pb.T, w.d, device="cuda")
+    set_rows(x, np.concatenate([seeded_rows(int(length[i]), w.d, seeds[i]) for i in order]))
+    ws = torch.empty(B.vfm_workspace_size(model.cfg, pb.c, model.lora_c(0)), dtype=torch.uint8, device="cuda")
+    B.vfm_layer_forward(model.cfg, model.c_layers[0], model.lora_c(0), pb.c, x, workspace=ws)
+    got, cu = x.cpu(), np.concatenate([[0], np.cumsum(length[order])])
+    out = [None] * len(task)
+    for p, i in enumerate(order):
+        out[i] = got[int(cu[p]):int(cu[p + 1])]
+    return out
+
+
+@pytest.mark.parametrize("idx,d,d_ff,ranks", [(4, 2048, 5504, [16, 0, 8]), (4, 1024, 2816, [8, 64, 0]),
+                                              (2, 768, 3072, [16, 0, 8]), (3, 1024, 2816, [0, 40, 8])])
+@pytest.mark.parametrize("lens", [[1, 40, 23], [64, 1, 63], [130, 64, 65], [200, 300, 523]])
+def test_small_batch_rows_same_in_any_tile(idx, d, d_ff, ranks, lens):
+    """Batches below the small-batch threshold: a request's rows are the same
+    bits alone and in batches that take another row tile (64, 128 or 256 rows
+    of the split-K GEMM, 64 or 128 of the direct one)."""
+    w = wl.WORKLOADS[idx].replace(d=d, n_heads=d // 128 if idx == 4 else d // 64, d_ff=d_ff, n_tasks=3,
+                                  lora_targets=wl.PROJ if idx == 4 else ("q", "v", "o", "up", "down"))
+    model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=0.05)
+    log(f"small batch {w.name} d={d} lens={lens}")
+    whole = _rows_of(w, model, [2, 0, 1], lens, [5, 6, 7])
+    for i, t in enumerate([2, 0, 1]):
+        alone = _rows_of(w, model, [t], [lens[i]], [5 + i])[0]
+        assert torch.equal(alone, whole[i]), f"request {i} of {lens}"
+
+
+@pytest.mark.parametrize("idx,more", [(2, [1024 - 197]), (2, [5000]), (3, [1000]), (3, [9000])])
+def test_large_batch_rows_same_in_any_tile(idx, more):
+    """From the threshold on: the same bits from the 64- and 128-row tiles of
+    batches that cannot fill the chip and the 256-row ones of batches that can."""
+    w = wl.WORKLOADS[idx].replace(n_tasks=3, lora_targets=("q", "k", "v", "o", "up", "down"))
+    model = R.Model(w, n_layers=1, ranks=np.asarray([16, 0, 8], np.int32), b_std=0.05)
+    split = lambda n: [256] * (n // 256) + ([n % 256] if n % 256 else [])   # noqa: E731
+    log(f"large batch {w.name} beside {more} rows")
+    base = _rows_of(w, model, [1] + [0] * len(split(20000)), [197] + split(20000), [9] + list(range(20, 20 + 79)))[0]
+    got = _rows_of(w, model, [1] + [2] * len(split(more[0])), [197] + split(more[0]),
+                   [9] + list(range(200, 200 + len(split(more[0])))))[0]
+    assert torch.equal(base, got)
+
+
 def _layer_case(w, task, length, ranks, seed=1, b_std=0.05):
     batch = wl.Batch(np.asarray(task, np.int32), np.asarray(length, np.int32), None)
     model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=b_std, seed=seed)
@@ -101,4 +149,15 @@ def test_f32_layer_tiles(lens, family, hd, d_ff):
     log(f"f32 {family} lens={lens} hd={hd} f={d_ff}")
     task = [4, 1, 0, 3, 1][:len(lens)]
     out = _layer_case(w, task, lens, [8, 64, 0, 32, 16])
+    _check_layer(w, out[0], out[1], out[2], out[3], range(len(lens)))
+
+
+@pytest.mark.parametrize("idx,lens", [(2, [1]), (2, [63, 1, 1]), (2, [129, 64]), (2, [511, 512]), (3, [1, 2, 60, 1]),
+                                      (3, [300, 64, 256, 400]), (2, [1100, 3, 90]), (3, [700, 40, 333, 1])])
+def test_direct_tiles_against_oracle(idx, lens):
+    """Encoder layers on the 64- and 128-row tiles, both sides of the
+    small-batch threshold, every rank class and a bare task."""
+    w = wl.WORKLOADS[idx].replace(n_tasks=4, lora_targets=("q", "k", "v", "o", "up", "down"))
+    log(f"direct tiles {w.name} lens={lens}")
+    out = _layer_case(w, [3, 0, 2, 3][:len(lens)], lens, [8, 16, 0, 16] if len(lens) < 4 else [8, 16, 64, 32], b_std=0.03)
     _check_layer(w, out[0], out[1], out[2], out[3], range(len(lens)))
