@@ -436,7 +436,7 @@ int layer_impl(const vfm_cfg& c, const vfm_layer_weights* w, const vfm_lora_tabl
       // into each row's U and adds U B_t^T to the row's columns
       ShrinkSplitArgs a = {};
       a.X = X; a.ldx = K; a.K = K; a.P = P; a.ldp = ldu; a.rpad = rpad;
-      a.kchunks = shrink_chunks(K); a.rank = lora->rank;
+      a.kchunk = SHRINK_CHUNK; a.kchunks = shrink_chunks(K); a.rank = lora->rank;
       a.nsub = std::min(std::max(1, (lora->max_rank + 15) / 16), rpad / 16);
       for (int p : projs) {
         if (!has(p)) continue;
@@ -444,7 +444,8 @@ int layer_impl(const vfm_cfg& c, const vfm_layer_weights* w, const vfm_lora_tabl
         a.ucol[a.n_proj] = p * rpad;
         a.n_proj++;
       }
-      VFM_TIMED(VFM_PROF_SHRINK, launch_shrink_split(pl, a, s));
+      if (skinny_takes_shrink(T)) { k.sh = a; k.pl = pl; }
+      else VFM_TIMED(VFM_PROF_SHRINK, launch_shrink_split(pl, a, s));
       FinLora& fl = fa.lora;
       fl.enabled = 1;
       fl.P = P; fl.ldp = ldu; fl.cstride = (int64_t)T * ldu; fl.kchunks = a.kchunks;

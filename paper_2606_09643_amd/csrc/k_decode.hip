@@ -13,7 +13,8 @@
 //                  do not depend on scheduling.
 //   shrink_split   P[c, m, slot + j] = sum over K chunk c of X[m, k] A_t[j, k]:
 //                  one block per (task row tile, K chunk), so a task's A
-//                  factors are read once, by many blocks at a time.
+//                  factors are read once, by many blocks at a time; up to 64
+//                  rows in blocks of the GEMM's launch.
 //   finalize       per row: U = bf16(s_t * sum_c P) rebuilt in LDS, then
 //                  y = sum of the slices + U B_t^T + bias and the activation
 //                  or residual epilogue, streamed one thread per 4 outputs
@@ -36,6 +37,90 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 __device__ __forceinline__ int swz(int row, int kc) { return kc ^ ((row >> 1) & 7); }
 
 constexpr int SBK = 64;
+
+// ---------------------------------------------------------------------------
+// Split-K segmented shrink: one wave's 16 rows from row m0 (rows below r1 are
+// the tile's) of task t, NP projections from pp0 on, columns of K chunk c; A
+// rows feed the MFMA A slot, X rows the B slot.
+// ---------------------------------------------------------------------------
+template <int NP, int NSUB>
+__device__ __forceinline__ void shrink_split_rows(const Plan& pl, const ShrinkSplitArgs& a, int t, int m0, int r1,
+                                                  int c, int pp0, int lane) {
+  const int rank = min(a.rank[t], NSUB * 16);
+  const int m = m0 + (lane & 15);
+  const int k0 = c * a.kchunk, k1 = min(k0 + a.kchunk, a.K);
+  f32x4 acc[NP][NSUB];
+#pragma unroll
+  for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) acc[pp][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (rank > 0 && m0 < r1) {
+    const bf16* xrow = (const bf16*)a.X + (int64_t)min(m, r1 - 1) * a.ldx + 8 * (lane >> 4);
+    const bf16* arow[NP][NSUB];
+    bool on[NSUB];
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) on[s] = s * 16 + (lane & 15) < rank;
+#pragma unroll
+    for (int pp = 0; pp < NP; ++pp) {
+      const bf16* At = (const bf16*)a.A[pp0 + pp][t];
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+        arow[pp][s] = At + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + 8 * (lane >> 4);
+    }
+#pragma unroll 4
+    for (int k = k0; k < k1; k += 32) {
+      const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xrow + k);
+#pragma unroll
+      for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+        for (int s = 0; s < NSUB; ++s) {
+          bf16x8 af = *reinterpret_cast<const bf16x8*>(arow[pp][s] + k);
+          if (!on[s]) af = bf16x8{};
+          acc[pp][s] = mfma16(af, xf, acc[pp][s]);
+        }
+    }
+  }
+  if (m < r1) {
+    float* P = a.P + ((int64_t)c * pl.T + m) * a.ldp;
+#pragma unroll
+    for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+        *reinterpret_cast<float4*>(P + a.ucol[pp0 + pp] + s * 16 + 4 * (lane >> 4)) =
+            make_float4(acc[pp][s][0], acc[pp][s][1], acc[pp][s][2], acc[pp][s][3]);
+  }
+}
+
+// A launch of its own: block (row tile, K chunk), wave w takes rows 16 w ..
+template <int NP, int NSUB>
+__global__ __launch_bounds__(256) void shrink_split_kernel(Plan pl, ShrinkSplitArgs a) {
+  __shared__ int s_task;
+  const int tile = blockIdx.x;
+  const int t = block_tile_task(pl, tile, &s_task);
+  const int r0 = pl.seg_row[t] + (tile - pl.rtile_off[t]) * VFM_ROW_TILE;
+  const int r1 = min(r0 + VFM_ROW_TILE, pl.seg_row[t + 1]);
+  shrink_split_rows<NP, NSUB>(pl, a, t, r0 + (threadIdx.x >> 6) * 16, r1, blockIdx.y, 0, threadIdx.x & 63);
+}
+
+// Part of the split GEMM's launch: wave item (row tile, projection, K chunk),
+// the tile's 16-row groups one after the other.
+__device__ __forceinline__ void shrink_split_item(const Plan& pl, const ShrinkSplitArgs& a, int item, int lane) {
+  const int c = item % a.kchunks, pp = item / a.kchunks % a.n_proj, tile = item / a.kchunks / a.n_proj;
+  if (tile >= pl.n_rtiles) return;             // wave-uniform
+  int t = 0;                                   // the tile's task: found by the wave in one round of loads
+  for (int i = lane; i < (pl.n_tasks + 63 & ~63); i += 64) {
+    const bool mine = i < pl.n_tasks && pl.rtile_off[i] <= tile && tile < pl.rtile_off[i + 1];
+    const uint64_t who = __ballot(mine);
+    if (who) t = i - lane + (int)__builtin_ctzll(who);
+  }
+  const int r0 = pl.seg_row[t] + (tile - pl.rtile_off[t]) * VFM_ROW_TILE;
+  const int r1 = min(r0 + VFM_ROW_TILE, pl.seg_row[t + 1]);
+  for (int m0 = r0; m0 < r1; m0 += 16) {
+    if (a.nsub <= 1) shrink_split_rows<1, 1>(pl, a, t, m0, r1, c, pp, lane);
+    else if (a.nsub == 2) shrink_split_rows<1, 2>(pl, a, t, m0, r1, c, pp, lane);
+    else shrink_split_rows<1, 4>(pl, a, t, m0, r1, c, pp, lane);
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Split-K GEMM, BM rows x BN = 64 * NWN columns per block, 4 x NWN waves of
@@ -65,7 +150,7 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);   // vmcnt(N), lgkmcnt / expcnt not waited
 }
 
-template <int BM, int NWN, int WST>
+template <int BM, int NWN, int WST, bool SHRINK>
 __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   // loader waves: half for each operand, except 192 columns (12 waves), whose
   // activation rows need a power-of-two share (8 activation, 4 weight)
@@ -79,12 +164,20 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   // wave index in an SGPR, so the loader roles below are scalar branches
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 3, wn = wave >> 2;
+  if constexpr (SHRINK) {
+    // the first nsh blocks (a multiple of 8) run the split shrink of the same X
+    if ((int)blockIdx.x < a.nsh) {
+      if (blockIdx.y == 0) shrink_split_item(a.pl, a.sh, blockIdx.x * NW + wave, lane);
+      return;
+    }
+  }
+  const int nsh = SHRINK ? a.nsh : 0;
   const int ntn = (a.N + BN - 1) / BN;
   // consecutive blocks land on one XCD (the dispatcher deals block ids out
   // to the 8 XCDs in turn), so the blocks of one K split share that XCD's
   // L2 copy of the split's activation columns; the grid is padded to a
   // multiple of 8 and the padding blocks leave at once
-  const int bx = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int bx = (blockIdx.x & 7) * ((gridDim.x - nsh) >> 3) + ((blockIdx.x - nsh) >> 3);
   if (bx >= ntn * a.nsplit) return;
   const int tn = bx % ntn, split = bx / ntn;
   const int m0 = blockIdx.y * BM, n0 = tn * BN;
@@ -205,64 +298,6 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
       *reinterpret_cast<float4*>(Zs + (int64_t)m * a.N + n) =
           make_float4(acc[mi][ni][0], acc[mi][ni][1], acc[mi][ni][2], acc[mi][ni][3]);
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Split-K segmented shrink.  Each wave owns 16 rows of the tile and every
-// projection of the group; A rows feed the MFMA A slot, X rows the B slot.
-// ---------------------------------------------------------------------------
-template <int NP, int NSUB>
-__global__ __launch_bounds__(256) void shrink_split_kernel(Plan pl, ShrinkSplitArgs a) {
-  __shared__ int s_task;
-  const int tile = blockIdx.x, c = blockIdx.y;
-  const int t = block_tile_task(pl, tile, &s_task);
-  const int r0 = pl.seg_row[t] + (tile - pl.rtile_off[t]) * VFM_ROW_TILE;
-  const int r1 = min(r0 + VFM_ROW_TILE, pl.seg_row[t + 1]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rank = min(a.rank[t], NSUB * 16);
-  const int m = r0 + wave * 16 + (lane & 15);
-  const int k0 = c * a.kchunk, k1 = min(k0 + a.kchunk, a.K);
-  const bf16* X = (const bf16*)a.X;
-  f32x4 acc[NP][NSUB];
-#pragma unroll
-  for (int pp = 0; pp < NP; ++pp)
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) acc[pp][s] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (rank > 0 && r0 + wave * 16 < r1) {
-    const bf16* xrow = X + (int64_t)min(m, r1 - 1) * a.ldx + 8 * (lane >> 4);
-    const bf16* arow[NP][NSUB];
-    bool on[NSUB];
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) on[s] = s * 16 + (lane & 15) < rank;
-#pragma unroll
-    for (int pp = 0; pp < NP; ++pp) {
-      const bf16* At = (const bf16*)a.A[pp][t];
-#pragma unroll
-      for (int s = 0; s < NSUB; ++s)
-        arow[pp][s] = At + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + 8 * (lane >> 4);
-    }
-#pragma unroll 4
-    for (int k = k0; k < k1; k += 32) {
-      const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xrow + k);
-#pragma unroll
-      for (int pp = 0; pp < NP; ++pp)
-#pragma unroll
-        for (int s = 0; s < NSUB; ++s) {
-          bf16x8 af = *reinterpret_cast<const bf16x8*>(arow[pp][s] + k);
-          if (!on[s]) af = bf16x8{};
-          acc[pp][s] = mfma16(af, xf, acc[pp][s]);
-        }
-    }
-  }
-  if (m < r1) {
-    float* P = a.P + ((int64_t)c * pl.T + m) * a.ldp;
-#pragma unroll
-    for (int pp = 0; pp < NP; ++pp)
-#pragma unroll
-      for (int s = 0; s < NSUB; ++s)
-        *reinterpret_cast<float4*>(P + a.ucol[pp] + s * 16 + 4 * (lane >> 4)) =
-            make_float4(acc[pp][s][0], acc[pp][s][1], acc[pp][s][2], acc[pp][s][3]);
   }
 }
 
@@ -419,16 +454,25 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& a0, hipStream_t s) {
   SkinnyArgs a = a0;
   int bn;
   skinny_shape(a.N, a.K, &bn, &a.nsplit);
-  const int ntn = (a.N + bn - 1) / bn;
+  // up to 64 rows: 128-column blocks of 80 KB of LDS, two per CU, whatever
+  // the width the split was chosen for (the split alone fixes the sums), and
+  // the shrink's blocks beside them: one 7B decode row, shrink + GEMM of QKV /
+  // O / gate+up / down 23.6 / 13.5 / 34.7 / 25.5 us in launches of their own,
+  // 19.5 / 9.8 / 32.8 / 20.2 us together.  At 100 rows (60 tasks) the shrink's
+  // blocks hold up the GEMM's by what their launch costs: kept apart there.
   const int bm = a.M <= 64 ? 64 : a.M <= 128 ? 128 : 256;
-  dim3 grid((ntn * a.nsplit + 7) & ~7, (a.M + bm - 1) / bm);
-#define VFM_SK(BM_)                                                                                         \
-  do {                                                                                                      \
-    if (bn == 128) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 2, 4>), grid, dim3(512), 0, s, a);           \
-    else if (bn == 192) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 3, 4>), grid, dim3(768), 0, s, a);      \
-    else hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 4, 3>), grid, dim3(1024), 0, s, a);                    \
+  if (bm == 64) bn = 128;
+  const int ntn = (a.N + bn - 1) / bn;
+  a.nsh = a.sh.n_proj > 0 ? ((a.pl.n_rtiles * a.sh.kchunks * a.sh.n_proj + 7) / 8 + 7) & ~7 : 0;
+  if (a.nsh > 0 && bm != 64) return hipErrorInvalidValue;
+  dim3 grid(((ntn * a.nsplit + 7) & ~7) + a.nsh, (a.M + bm - 1) / bm);
+#define VFM_SK(BM_)                                                                                           \
+  do {                                                                                                        \
+    if (bn == 128) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 2, 4, false>), grid, dim3(512), 0, s, a);      \
+    else if (bn == 192) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 3, 4, false>), grid, dim3(768), 0, s, a); \
+    else hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 4, 3, false>), grid, dim3(1024), 0, s, a);               \
   } while (0)
-  if (bm == 64) VFM_SK(64);
+  if (bm == 64) hipLaunchKernelGGL((gemm_skinny_kernel<64, 2, 4, true>), grid, dim3(512), 0, s, a);
   else if (bm == 128) VFM_SK(128);
   else VFM_SK(256);
 #undef VFM_SK
@@ -437,12 +481,11 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& a0, hipStream_t s) {
 
 // K chunks of the split shrink: fixed 256-column chunks (the last one
 // ragged), independent of the batch for the same reason as the GEMM split.
-int shrink_chunks(int K) { return (K + 255) / 256; }
+int shrink_chunks(int K) { return (K + SHRINK_CHUNK - 1) / SHRINK_CHUNK; }
 
 hipError_t launch_shrink_split(const Plan& pl, const ShrinkSplitArgs& a0, hipStream_t s) {
   if (pl.n_rtiles == 0 || a0.n_proj == 0) return hipSuccess;
-  ShrinkSplitArgs a = a0;
-  a.kchunk = 256;
+  const ShrinkSplitArgs& a = a0;
   dim3 grid(pl.n_rtiles, a.kchunks);
 #define VFM_SS(NP_, NS_) hipLaunchKernelGGL((shrink_split_kernel<NP_, NS_>), grid, dim3(256), 0, s, pl, a)
   // only the sub-tiles the table's largest rank reaches: 1 (rank <= 16), 2 (<= 32) or 4

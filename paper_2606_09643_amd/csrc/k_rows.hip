@@ -91,22 +91,31 @@ __device__ inline void norm_row_regs(const float* xr, int d, const TW* g, const 
   }
 }
 
-// Few rows (decode): one 256-thread block per row, MAXC float4 chunks per
+// Few rows (decode): one block of NT threads per row, MAXC float4 chunks per
 // thread, block reductions through LDS, so a small batch still keeps every
 // CU busy.
-// Normalise one row held by a 256-thread block (MAXC float4 chunks per
-// thread in v) and store it; block reductions through red.
-template <typename T, int MAXC>
+// Normalise one row held by such a block (its chunks in v) and store it;
+// block reductions through red, the waves' sums added in wave order, pairwise
+// by fours.
+template <int NW>
+__device__ __forceinline__ float sum_waves(const float (&r)[NW]) {
+  float s = (r[0] + r[1]) + (r[2] + r[3]);
+#pragma unroll
+  for (int w = 4; w < NW; w += 4) s += (r[w] + r[w + 1]) + (r[w + 2] + r[w + 3]);
+  return s;
+}
+
+template <typename T, int MAXC, int NT = 256>
 __device__ inline void norm_block_row(const float4 (&v)[MAXC], int d, const T* __restrict__ g,
                                       const T* __restrict__ b, int kind, float eps, T* __restrict__ o,
-                                      float (&red)[2][4]) {
+                                      float (&red)[2][NT / 64]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nch = d >> 2;
   float4 gg[MAXC], bb[MAXC];
   float sum = 0.f;
 #pragma unroll
   for (int i = 0; i < MAXC; ++i) {
-    const int c = tid + 256 * i;
+    const int c = tid + NT * i;
     if (c < nch) {
       gg[i] = load4<T>(g + 4 * c);
       bb[i] = b ? load4<T>(b + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -118,12 +127,12 @@ __device__ inline void norm_block_row(const float4 (&v)[MAXC], int d, const T* _
     sum = wave_sum(sum);
     if (lane == 0) red[0][wave] = sum;
     __syncthreads();
-    mean = ((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])) / (float)d;
+    mean = sum_waves(red[0]) / (float)d;
   }
   float sq = 0.f;
 #pragma unroll
   for (int i = 0; i < MAXC; ++i) {
-    const int c = tid + 256 * i;
+    const int c = tid + NT * i;
     if (c < nch) {
       const float a = v[i].x - mean, b2 = v[i].y - mean, cc = v[i].z - mean, dd = v[i].w - mean;
       sq += (a * a + b2 * b2) + (cc * cc + dd * dd);
@@ -132,10 +141,10 @@ __device__ inline void norm_block_row(const float4 (&v)[MAXC], int d, const T* _
   sq = wave_sum(sq);
   if (lane == 0) red[1][wave] = sq;
   __syncthreads();
-  const float rstd = rsqrtf(((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])) / (float)d + eps);
+  const float rstd = rsqrtf(sum_waves(red[1]) / (float)d + eps);
 #pragma unroll
   for (int i = 0; i < MAXC; ++i) {
-    const int c = tid + 256 * i;
+    const int c = tid + NT * i;
     if (c < nch) {
       float4 y;
       y.x = (v[i].x - mean) * rstd * gg[i].x + bb[i].x;
@@ -166,13 +175,17 @@ __global__ __launch_bounds__(256) void norm_rows_block_kernel(const float* __res
 }
 
 // Residual finalize + pre-norm, one block per row: x += (sum of the partial
-// slices) + bias, then the row is normalised into h.
-template <typename T, int MAXC>
-__global__ __launch_bounds__(256) void finalize_norm_kernel(FinalizeArgs a, const T* __restrict__ g,
+// slices) + bias, then the row is normalised into h.  Bound by the chain of a
+// row's dependent loads (partials of U, U, B rows, slices) and, for wide rows
+// in few threads, by taking them chunk after chunk: 1024 threads hold a row of
+// 4096 columns with one chunk each (1 / 37 / 256 rows: 14.0 / 16.8 / 21.3 us
+// with 256 threads of four chunks, 9.6 / 12.6 / 17.4 us so).
+template <typename T, int MAXC, int NT>
+__global__ __launch_bounds__(NT) void finalize_norm_kernel(FinalizeArgs a, const T* __restrict__ g,
                                                             const T* __restrict__ b, int kind, float eps,
                                                             T* __restrict__ h) {
-  __shared__ float red[2][4];
-  __shared__ float Us[3 * VFM_MAX_RANK], ured[256];
+  __shared__ float red[2][NT / 64];
+  __shared__ float Us[3 * VFM_MAX_RANK], ured[NT];
   // block b takes row (b % 8) * per + b / 8: consecutive rows (often one
   // task's) run on one XCD, so the task's B rows come from that XCD's L2
   const int per = gridDim.x / 8;
@@ -191,7 +204,7 @@ __global__ __launch_bounds__(256) void finalize_norm_kernel(FinalizeArgs a, cons
   float4 v[MAXC];
 #pragma unroll
   for (int i = 0; i < MAXC; ++i) {
-    const int c = tid + 256 * i;
+    const int c = tid + NT * i;
     v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (c < nch) {
       float4 s4 = sum_slices(a.Z + (int64_t)row * a.N + 4 * c, zs, a.nslices);
@@ -209,7 +222,7 @@ __global__ __launch_bounds__(256) void finalize_norm_kernel(FinalizeArgs a, cons
       v[i] = xv;
     }
   }
-  norm_block_row<T, MAXC>(v, a.N, g, b, kind, eps, h + (int64_t)row * a.N, red);
+  norm_block_row<T, MAXC, NT>(v, a.N, g, b, kind, eps, h + (int64_t)row * a.N, red);
 }
 
 template <typename T, int MAXI>
@@ -462,8 +475,14 @@ hipError_t launch_finalize_norm(int dtype, const FinalizeArgs& a, const void* g,
   if (a.M == 0) return hipSuccess;
   if (a.epi != EPI_RESID || dtype != VFM_BF16 || a.N % 4 || a.N > 8192 || a.ldo != a.N)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL((finalize_norm_kernel<bf16, 8>), dim3((a.M + 7) / 8 * 8), dim3(256), 0, s, a, (const bf16*)g,
-                     (const bf16*)b, kind, eps, (bf16*)h);
+#define FN(MC, NT)                                                                                            \
+  hipLaunchKernelGGL((finalize_norm_kernel<bf16, MC, NT>), dim3((a.M + 7) / 8 * 8), dim3(NT), 0, s, a,        \
+                     (const bf16*)g, (const bf16*)b, kind, eps, (bf16*)h)
+  // by the row's width alone (a row's sums do not depend on the batch)
+  if (a.N <= 1024) FN(1, 256);
+  else if (a.N <= 4096) FN(1, 1024);
+  else FN(2, 1024);
+#undef FN
   return hipGetLastError();
 }
 

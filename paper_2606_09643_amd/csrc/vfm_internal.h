@@ -273,19 +273,6 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 constexpr int VFM_DIRECT_K = 1024;
 
 // ---- small-batch (decode) projections, bf16 only -------------------------
-// Split-K shared GEMM into fp32 partials: Z[s, m, n] = sum over the s-th
-// K range of X[m, k] W[n, k]; rows n >= n_half of the stacked weight come
-// from W2 (SwiGLU: gate columns then up columns).
-struct SkinnyArgs {
-  const void* X; int ldx;
-  const void* W; const void* W2; int n_half;
-  int M, N, K;
-  int nsplit;
-  float* Z;
-};
-hipError_t launch_gemm_skinny(const SkinnyArgs& a, hipStream_t s);
-int skinny_splits(int N, int K);
-
 // Split-K segmented LoRA shrink into fp32 partials:
 // P[c, m, ucol[p] + j] = sum over K chunk c of X[m, k] A_{t,p}[j, k] for
 // j < rpad (zero past rank_t); kchunks chunks of kchunk columns.
@@ -298,7 +285,26 @@ struct ShrinkSplitArgs {
   const int32_t* rank;
 };
 hipError_t launch_shrink_split(const Plan& pl, const ShrinkSplitArgs& a, hipStream_t s);
+constexpr int SHRINK_CHUNK = 256;
 int shrink_chunks(int K);
+
+// Split-K shared GEMM into fp32 partials: Z[s, m, n] = sum over the s-th
+// K range of X[m, k] W[n, k]; rows n >= n_half of the stacked weight come
+// from W2 (SwiGLU: gate columns then up columns).
+struct SkinnyArgs {
+  const void* X; int ldx;
+  const void* W; const void* W2; int n_half;
+  int M, N, K;
+  int nsplit;
+  float* Z;
+  // with sh.n_proj > 0 the launch also runs the split shrink of X (in blocks
+  // of its own); needs skinny_takes_shrink(M)
+  ShrinkSplitArgs sh; Plan pl;
+  int nsh;                         // its blocks (set by the launcher)
+};
+hipError_t launch_gemm_skinny(const SkinnyArgs& a, hipStream_t s);
+inline bool skinny_takes_shrink(int M) { return M <= 64; }
+int skinny_splits(int N, int K);
 
 // Where the K / V of token k of plan position p live in a head-major cache:
 // slot kv_start[p] + k, or with a page table (original request order,
@@ -356,7 +362,7 @@ hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
 // K chunks c of P[c, m, ucol[i] + j]) for the slots with adapters and j < r
 // (r = the row's task rank, returned) and ends with a barrier.  All threads
 // share the sums: thread q takes element (i, j) = q % (n_slots * r) and
-// chunk group q / (n_slots * r) of G = blockDim / (n_slots * r) groups
+// chunk group q / (n_slots * r) of G = min(blockDim / (n_slots * r), 16) groups
 // (chunks g, g + G, ... added in increasing order, 8 loads in flight), and
 // the G group sums are added in group order through red[blockDim].  The
 // order follows from the row's rank and the weight's K split alone, never
@@ -367,7 +373,7 @@ __device__ __forceinline__ int fin_lora_u(const FinLora& L, int m, float* Us, fl
   const float sc = L.scale[t];
   const int ne = L.n_slots * r;                 // <= 3 * VFM_MAX_RANK = 192 < 256 threads
   if (ne == 0) return r;                        // block-uniform: no slot reads Us
-  const int G = blockDim.x / ne;
+  const int G = min((int)blockDim.x / ne, 16);
   const int q = threadIdx.x, g = q / ne, e = q - g * ne;
   float s = 0.f;
   if (g < G) {

@@ -161,3 +161,37 @@ def test_direct_tiles_against_oracle(idx, lens):
     log(f"direct tiles {w.name} lens={lens}")
     out = _layer_case(w, [3, 0, 2, 3][:len(lens)], lens, [8, 16, 0, 16] if len(lens) < 4 else [8, 16, 64, 32], b_std=0.03)
     _check_layer(w, out[0], out[1], out[2], out[3], range(len(lens)))
+
+
+@pytest.mark.parametrize("n", [1, 3, 33, 64, 65, 128, 129])
+@pytest.mark.parametrize("max_rank", [8, 32, 64])
+def test_decode_rows_same_beside_others(n, max_rank):
+    """Decode rows of the split-K path: the same bits alone (the shrink in the
+    GEMM's launch) and among n rows of other tasks, either side of 64 and 128
+    rows, ranks in each shrink width and a rank-0 task."""
+    w = wl.WORKLOADS[5].replace(d=2048, n_heads=16, d_ff=5504, n_tasks=70)
+    ranks = np.array([[0, 8, max_rank][t % 3] for t in range(70)], np.int32)
+    model = R.Model(w, n_layers=1, ranks=ranks, b_std=0.05)
+    r = np.random.default_rng(n)
+    task = np.concatenate([[1], r.integers(0, 70, size=n - 1)]).astype(np.int32)
+    ctx = np.concatenate([[77], r.integers(0, 200, size=n - 1)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    kv = torch.randn(2, 16, 78, 128, generator=g, device="cuda").to(torch.bfloat16)
+
+    def run(m):
+        slots = int((ctx[:m] + 1).sum())
+        start = np.concatenate([[0], np.cumsum(ctx[:m] + 1)[:-1]]).astype(np.int32)
+        pb = B.Batch(task[:m], np.ones(m, np.int32), 70, ctx_len=ctx[:m], kv_start=start)
+        order = np.argsort(task[:m], kind="stable")
+        rows = np.concatenate([seeded_rows(1, w.d, 3), seeded_rows(n, w.d, 4)])[:m][order]
+        k = torch.randn(16, slots, 128, generator=g, device="cuda").to(torch.bfloat16)
+        v = k.clone()
+        k[:, :78], v[:, :78] = kv[0], kv[1]
+        x = torch.empty(m, w.d, device="cuda")
+        set_rows(x, rows)
+        ws = torch.empty(B.vfm_workspace_size(model.cfg, pb.c, model.lora_c(0)), dtype=torch.uint8, device="cuda")
+        B.vfm_layer_forward(model.cfg, model.c_layers[0], model.lora_c(0), pb.c, x, k, v, slots, ws)
+        return x[int(np.nonzero(order == 0)[0][0])].cpu()
+
+    log(f"decode rows n={n} max_rank={max_rank}")
+    assert torch.equal(run(1), run(n))
