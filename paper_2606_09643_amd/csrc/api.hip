@@ -428,7 +428,7 @@ int layer_impl(const vfm_cfg& c, const vfm_layer_weights* w, const vfm_lora_tabl
     k.M = T; k.N = nz; k.K = K; k.Z = Z;
     k.nsplit = skinny_splits(nz, K);
     FinalizeArgs fa = {};
-    fa.Z = Z; fa.nslices = k.nsplit; fa.M = T; fa.N = N; fa.epi = epi; fa.bias = bias;
+    fa.Z = Z; fa.nslices = skinny_slices(T, nz, K); fa.M = T; fa.N = N; fa.epi = epi; fa.bias = bias;
     fa.out = out; fa.ldo = ldo;
     fa.rope = fin_rope;
     if (any) {

@@ -7,8 +7,9 @@
 // Three kernels per projection group replace the large-tile GEMM:
 //
 //   gemm_skinny    Z[s, m, n] = sum over K range s of X[m, k] W[n, k]:
-//                  256-row x BN-column tiles, two LDS stages fed by
-//                  global_load_lds, K split so the grid covers the chip.
+//                  row x column tiles, LDS rings fed by global_load_lds,
+//                  K split so the grid covers the chip (or, with enough
+//                  rows, every split walked by one block).
 //                  Partials stay per split (fp32, no atomics), so results
 //                  do not depend on scheduling.
 //   shrink_split   P[c, m, slot + j] = sum over K chunk c of X[m, k] A_t[j, k]:
@@ -128,8 +129,8 @@ __device__ __forceinline__ void shrink_split_item(const Plan& pl, const ShrinkSp
 //
 // Every weight element is used by the few hundred rows of one tile only, so
 // the weight stream comes from HBM at full latency while the activation
-// columns are L2 hits.  Half of the waves load activation stages (one step
-// ahead, two LDS stages), the other half weight stages (WST - 1 steps
+// columns are L2 hits.  Half of the waves load activation stages (XST - 1
+// steps ahead, XST LDS stages), the other half weight stages (WST - 1 steps
 // ahead, WST LDS stages): a wave's loads complete in issue order, so
 // keeping the two streams in different waves lets the short-latency
 // activation loads be waited on without waiting for the weight loads
@@ -141,16 +142,34 @@ __device__ __forceinline__ void shrink_split_item(const Plan& pl, const ShrinkSp
 // the weights.  One row of the 7B decoder, QKV / O / gate+up / down: 27.4 /
 // 12.3 / 47.2 / 28.0 us with 256-row tiles, 18.7 / 8.9 / 29.6 / 20.8 with 64
 // (5.4 / 3.8 / 6.1 / 4.3 TB/s of weights); deeper weight rings in the LDS that
-// this frees (6 or 8 stages) gained nothing.  The K steps and their order are
+// this frees (6 or 8 stages) gained nothing, deeper activation rings a little
+// (37 rows, down: 23.5 -> 21.0 us with 4 activation and 3 weight stages).  The
+// K steps and their order are
 // the same for every BM, and so are a row's sums.
 // ---------------------------------------------------------------------------
 template <int N>
 __device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 16, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | N);   // vmcnt(N), lgkmcnt / expcnt not waited
+  static_assert(N >= 0 && N < 64, "vmcnt field");
+  // vmcnt(N) (bits 3:0 and 15:14), lgkmcnt / expcnt not waited
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+// wait until at most `newer` steps (MAX at most) of R loads each are outstanding
+template <int R, int MAX>
+__device__ __forceinline__ void wait_newer(int newer) {
+  if constexpr (MAX == 0) {
+    wait_vm<0>();
+  } else {
+    if (newer >= MAX) wait_vm<MAX * R>();
+    else wait_newer<R, MAX - 1>(newer);
+  }
 }
 
-template <int BM, int NWN, int WST, bool SHRINK>
+//
+// WALK: a block walks every split of its tile, adding each split's sums to a
+// total (the finalize's order), and writes one slice.  With enough rows the
+// row tiles alone give every CU a block, and the splits' partials, written and
+// read back, are what is left to save.
+template <int BM, int NWN, int XST, int WST, bool SHRINK, bool WALK>
 __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   // loader waves: half for each operand, except 192 columns (12 waves), whose
   // activation rows need a power-of-two share (8 activation, 4 weight)
@@ -158,9 +177,8 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   constexpr int SA = BM * SBK, SB = BN * SBK;
   constexpr int XR = BM / (8 * XW), WR = BN / (8 * WW);    // 1 KB rounds per stage and loader wave
   static_assert(XR * 8 * XW == BM && WR * 8 * WW == BN, "loader rounds");
-  static_assert(WST == 3 || WST == 4, "weight stages");
-  static_assert(WR * (WST - 2) < 16, "vmcnt range");
-  __shared__ __attribute__((aligned(16))) bf16 smem[2 * SA + WST * SB];
+  static_assert(XST >= 2 && WST >= 2, "stages");
+  __shared__ __attribute__((aligned(16))) bf16 smem[XST * SA + WST * SB];
   // wave index in an SGPR, so the loader roles below are scalar branches
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 3, wn = wave >> 2;
@@ -178,12 +196,15 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   // L2 copy of the split's activation columns; the grid is padded to a
   // multiple of 8 and the padding blocks leave at once
   const int bx = (blockIdx.x & 7) * ((gridDim.x - nsh) >> 3) + ((blockIdx.x - nsh) >> 3);
-  if (bx >= ntn * a.nsplit) return;
-  const int tn = bx % ntn, split = bx / ntn;
-  const int m0 = blockIdx.y * BM, n0 = tn * BN;
+  // WALK: the row tiles of a column tile follow each other (one XCD's L2 then
+  // serves the weights to all but the first)
+  const int ntm = WALK ? (a.M + BM - 1) / BM : 1;
+  if (bx >= ntn * (WALK ? ntm : a.nsplit)) return;
+  const int tn = WALK ? bx / ntm : bx % ntn, split = WALK ? 0 : bx / ntn;
+  const int m0 = (WALK ? bx % ntm : (int)blockIdx.y) * BM, n0 = tn * BN;
   const int nkt = a.K / SBK;
-  const int kt0 = (int)((int64_t)split * nkt / a.nsplit);
-  const int kt1 = (int)((int64_t)(split + 1) * nkt / a.nsplit);
+  const int kt0 = WALK ? 0 : (int)((int64_t)split * nkt / a.nsplit);
+  const int kt1 = WALK ? nkt : (int)((int64_t)(split + 1) * nkt / a.nsplit);
   const int nk = kt1 - kt0;
 
   // loader rows: wave lw of its operand fills rows lw * 8 + (lane >> 3) +
@@ -209,12 +230,12 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
     }
   }
   bf16* const Xs = smem;
-  bf16* const Ws = smem + 2 * SA;
-  auto issue_x = [&](int j) {   // step j of the block's K range into X stage j & 1
+  bf16* const Ws = smem + XST * SA;
+  auto issue_x = [&](int j, int slot) {   // step j of the block's K range
 #pragma unroll
     for (int i = 0; i < XR; ++i)
       __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + j * SBK),
-                                       (lptr_t)(Xs + (j & 1) * SA + (i * XW + lw) * 512), 16, 0, 0);
+                                       (lptr_t)(Xs + slot * SA + (i * XW + lw) * 512), 16, 0, 0);
   };
   // the weights are read once per forward: nontemporal (cache policy 2, nt)
   auto issue_w = [&](int j, int slot) {
@@ -229,39 +250,33 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
   for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
     for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 tot[WALK ? FM : 1][WALK ? 4 : 1];
+  int sp = 1, next = WALK ? nkt / a.nsplit : 0;   // the split after the current one, and where it starts
+  bool first = true;
   if (nk > 0) {
     if (xload) {
-      issue_x(0);
+#pragma unroll
+      for (int j = 0; j < XST - 1; ++j)
+        if (j < nk) issue_x(j, j);
     } else {
 #pragma unroll
       for (int j = 0; j < WST - 1; ++j)
         if (j < nk) issue_w(j, j);
     }
-    int ws = 0;                                   // W stage of step j
+    int xs = 0, ws = 0;                           // stages of step j
     for (int j = 0; j < nk; ++j) {
-      // this wave's loads of step j have landed: the X loaders have nothing
-      // newer in flight, the W loaders up to WST - 2 newer steps
-      if (xload) {
-        wait_vm<0>();
-      } else {
-        const int newer = min(nk - 1 - j, WST - 2);
-        if constexpr (WST >= 4) {
-          if (newer >= 2) wait_vm<2 * WR>();
-          else if (newer == 1) wait_vm<WR>();
-          else wait_vm<0>();
-        } else {
-          if (newer >= 1) wait_vm<WR>();
-          else wait_vm<0>();
-        }
-      }
+      // this wave's loads of step j have landed, up to XST - 2 (WST - 2) newer
+      // steps are in flight
+      if (xload) wait_newer<XR, XST - 2>(min(nk - 1 - j, XST - 2));
+      else wait_newer<WR, WST - 2>(min(nk - 1 - j, WST - 2));
       __builtin_amdgcn_s_barrier();
       // every wave is past step j - 1, whose X stage and W stage are free
       if (xload) {
-        if (j + 1 < nk) issue_x(j + 1);
+        if (j + XST - 1 < nk) issue_x(j + XST - 1, xs == 0 ? XST - 1 : xs - 1);
       } else {
         if (j + WST - 1 < nk) issue_w(j + WST - 1, ws == 0 ? WST - 1 : ws - 1);
       }
-      const bf16* As = Xs + (j & 1) * SA;
+      const bf16* As = Xs + xs * SA;
       const bf16* Bs = Ws + ws * SB;
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
@@ -282,7 +297,22 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
 #pragma unroll
           for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = mfma16(wf[ni], xf[mi], acc[mi][ni]);
       }
+      xs = xs == XST - 1 ? 0 : xs + 1;
       ws = ws == WST - 1 ? 0 : ws + 1;
+      if constexpr (WALK) {
+        if (j + 1 == next) {                        // block-uniform: the end of a split
+#pragma unroll
+          for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 4; ++ni) {
+              tot[mi][ni] = first ? acc[mi][ni] : tot[mi][ni] + acc[mi][ni];
+              acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+          first = false;
+          ++sp;
+          next = (int)((int64_t)sp * nkt / a.nsplit);
+        }
+      }
     }
   }
   // lane holds D[n = 4 * (lane >> 4) + i][m = lane & 15] of each 16 x 16 block
@@ -295,8 +325,9 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
     for (int ni = 0; ni < 4; ++ni) {
       const int n = n0 + wn * 64 + ni * 16 + 4 * (lane >> 4);
       if (n >= a.N) continue;
-      *reinterpret_cast<float4*>(Zs + (int64_t)m * a.N + n) =
-          make_float4(acc[mi][ni][0], acc[mi][ni][1], acc[mi][ni][2], acc[mi][ni][3]);
+      f32x4 v = acc[mi][ni];
+      if constexpr (WALK) v = tot[mi][ni];
+      *reinterpret_cast<float4*>(Zs + (int64_t)m * a.N + n) = make_float4(v[0], v[1], v[2], v[3]);
     }
   }
 }
@@ -441,6 +472,32 @@ void skinny_shape(int N, int K, int* bn, int* nsplit) {
   }
 }
 
+// The walking launch's tile for an M-row batch, or bm 0 for the split launch:
+// the faster one by an estimate (us) fitted on 200 to 1000 rows of the 7B
+// decoder's weights.  A block's K step takes what its waves need from barrier
+// to barrier, whatever the depth of the rings; one block per CU runs at a
+// time.  The split launch also writes and reads back nsplit - 1 more slices of
+// 4 M N bytes.  333 rows: QKV 65.0 -> 55.9 us as 128 x 192, gate+up 105.2 ->
+// 71.4 as 192 x 192, the finalizes 36.2 / 42.4 -> 28.6 / 35.0; O and down stay
+// split (33.3, 66.4 against 44.1, 108.4).  1000 rows: QKV 135.8 -> 94.9, gate+up
+// 210.2 -> 178.1, O 65.7 -> 49.6, down 131.6 -> 119.0.
+struct Walk { int bm, bn; };
+Walk skinny_walk(int M, int N, int K, int split_bn, int nsplit) {
+  Walk best = {0, 0};
+  if (M <= 128 || nsplit < 2) return best;
+  const double nkt = K / SBK;
+  const double step = split_bn == 128 ? 1.2 : split_bn == 192 ? 1.55 : 1.9;
+  double cost = (M + 255) / 256 * (nkt / nsplit * step + 7.0) + (nsplit - 1) * 4e-6 * M * N / 6.6;
+  constexpr struct { int bm, bn; double step; } cand[4] = {
+      {128, 128, 0.62}, {128, 192, 0.78}, {192, 192, 1.0}, {256, 192, 1.32}};
+  for (const auto& c : cand) {
+    const int tiles = (N + c.bn - 1) / c.bn * ((M + c.bm - 1) / c.bm);
+    const double t = (tiles + 255) / 256 * (nkt * c.step + 6.0);
+    if (t < cost) { cost = t; best = {c.bm, c.bn}; }
+  }
+  return best;
+}
+
 }  // namespace
 
 int skinny_splits(int N, int K) {
@@ -466,17 +523,33 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& a0, hipStream_t s) {
   a.nsh = a.sh.n_proj > 0 ? ((a.pl.n_rtiles * a.sh.kchunks * a.sh.n_proj + 7) / 8 + 7) & ~7 : 0;
   if (a.nsh > 0 && bm != 64) return hipErrorInvalidValue;
   dim3 grid(((ntn * a.nsplit + 7) & ~7) + a.nsh, (a.M + bm - 1) / bm);
+  const Walk wk = skinny_walk(a.M, a.N, a.K, bn, a.nsplit);
+  if (wk.bm > 0) {
+    const int tiles = (a.N + wk.bn - 1) / wk.bn * ((a.M + wk.bm - 1) / wk.bm);
+    const dim3 g((tiles + 7) & ~7);
+    if (wk.bm == 256) hipLaunchKernelGGL((gemm_skinny_kernel<256, 3, 2, 4, false, true>), g, dim3(768), 0, s, a);
+    else if (wk.bm == 192) hipLaunchKernelGGL((gemm_skinny_kernel<192, 3, 3, 3, false, true>), g, dim3(768), 0, s, a);
+    else if (wk.bn == 192) hipLaunchKernelGGL((gemm_skinny_kernel<128, 3, 4, 4, false, true>), g, dim3(768), 0, s, a);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<128, 2, 4, 4, false, true>), g, dim3(512), 0, s, a);
+    return hipGetLastError();
+  }
 #define VFM_SK(BM_)                                                                                           \
   do {                                                                                                        \
-    if (bn == 128) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 2, 4, false>), grid, dim3(512), 0, s, a);      \
-    else if (bn == 192) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 3, 4, false>), grid, dim3(768), 0, s, a); \
-    else hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 4, 3, false>), grid, dim3(1024), 0, s, a);               \
+    if (bn == 128) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 2, BM_ == 256 ? 3 : 4, 4, false, false>), grid, dim3(512), 0, s, a); \
+    else if (bn == 192) hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 3, BM_ == 256 ? 2 : 4, 4, false, false>), grid, dim3(768), 0, s, a); \
+    else hipLaunchKernelGGL((gemm_skinny_kernel<BM_, 4, 2, 3, false, false>), grid, dim3(1024), 0, s, a);        \
   } while (0)
-  if (bm == 64) hipLaunchKernelGGL((gemm_skinny_kernel<64, 2, 4, true>), grid, dim3(512), 0, s, a);
+  if (bm == 64) hipLaunchKernelGGL((gemm_skinny_kernel<64, 2, 4, 3, true, false>), grid, dim3(512), 0, s, a);
   else if (bm == 128) VFM_SK(128);
   else VFM_SK(256);
 #undef VFM_SK
   return hipGetLastError();
+}
+
+int skinny_slices(int M, int N, int K) {
+  int bn, ns;
+  skinny_shape(N, K, &bn, &ns);
+  return skinny_walk(M, N, K, bn, ns).bm > 0 ? 1 : ns;
 }
 
 // K chunks of the split shrink: fixed 256-column chunks (the last one

@@ -128,28 +128,27 @@ __device__ __forceinline__ float4 load4_nt(const float* p) {
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// Sum of ns fp32 partial slices (stride zs floats) at z, 4 columns, in a
-// fixed order: slice j goes to lane j mod 4 of four running sums, which are
-// then added pairwise.  Each partial is read once: nontemporal loads.
+// Sum of ns fp32 partial slices (stride zs floats) at z, 4 columns, in slice
+// order (the order in which a block that walks every split adds them up).
+// Each partial is read once: nontemporal loads.
 __device__ __forceinline__ float4 sum_slices(const float* z, int64_t zs, int ns) {
-  float4 s4[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) s4[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-  int sp = 0;
+  float4 s = load4_nt(z);
+  int sp = 1;
   for (; sp + 4 <= ns; sp += 4) {
     float4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = load4_nt(z + (sp + j) * zs);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) add4(s4[j], v[j]);
+    for (int j = 0; j < 4; ++j) add4(s, v[j]);
   }
+  float4 v[3];
 #pragma unroll
-  for (int j = 0; j < 3; ++j)  // the last ns mod 4 slices
-    if (sp + j < ns) add4(s4[j], load4_nt(z + (sp + j) * zs));
-  add4(s4[0], s4[1]);
-  add4(s4[2], s4[3]);
-  add4(s4[0], s4[2]);
-  return s4[0];
+  for (int j = 0; j < 3; ++j)  // the last (ns - 1) mod 4 slices
+    if (sp + j < ns) v[j] = load4_nt(z + (sp + j) * zs);
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (sp + j < ns) add4(s, v[j]);
+  return s;
 }
 
 __device__ inline float to_f32(float v) { return v; }
@@ -302,6 +301,9 @@ struct SkinnyArgs {
   ShrinkSplitArgs sh; Plan pl;
   int nsh;                         // its blocks (set by the launcher)
 };
+// Slices of Z that the launch writes: skinny_splits(N, K), or 1 when its blocks
+// walk every split themselves (the splits' sums added in order: the same bits).
+int skinny_slices(int M, int N, int K);
 hipError_t launch_gemm_skinny(const SkinnyArgs& a, hipStream_t s);
 inline bool skinny_takes_shrink(int M) { return M <= 64; }
 int skinny_splits(int N, int K);

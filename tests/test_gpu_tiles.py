@@ -195,3 +195,17 @@ def test_decode_rows_same_beside_others(n, max_rank):
 
     log(f"decode rows n={n} max_rank={max_rank}")
     assert torch.equal(run(1), run(n))
+
+
+@pytest.mark.parametrize("lens", [[129], [150, 106], [333, 200], [512, 70], [900, 123]])
+def test_walked_splits_same_as_split_launch(lens):
+    """Prompt batches wide enough that a block walks every K split of its tile
+    (each of its tile shapes, whole and ragged) give a request the bits that
+    the split launch gives it alone (at most 128 rows)."""
+    w = wl.WORKLOADS[4].replace(d=4096, d_ff=11008, n_tasks=3)
+    model = R.Model(w, n_layers=1, ranks=np.asarray([16, 0, 8], np.int32), b_std=0.05)
+    log(f"walked splits lens={lens}")
+    alone = _rows_of(w, model, [2], [100], [5])[0]
+    whole = _rows_of(w, model, [2] + [0, 1][:len(lens)], [100] + [n - 100 if i == 0 else n for i, n in enumerate(lens)],
+                     [5, 6, 7][:len(lens) + 1])[0]
+    assert torch.equal(alone, whole)
