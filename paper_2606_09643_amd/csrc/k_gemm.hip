@@ -387,357 +387,10 @@ __device__ __forceinline__ void wait_steps(int later) {
   }
 }
 
-// One output tile, WM x 2 waves, NST LDS stages.
-template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK, int WM, int NST>
-__device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& a) {
-  constexpr int NW = 2 * WM, NTH = 64 * NW, WN = 2, TM = BMT / WM, TN = BNT / 2, FM = TM / 16, FN = TN / 16;
-  constexpr int ACH = BMT * 8 / NTH, BCH = BNT * 8 / NTH;  // 16-byte chunks per lane and stage
-  constexpr int SA = BMT * BK, SB = BNT * BK;
-  constexpr bool EARLY = WM == 2;                            // small tiles: latency bound
-  static_assert(BMT % 64 == 0 && BNT % 64 == 0 && FN % 2 == 0, "tile shape");
-  constexpr int RSTEP = NTH / 8;                             // rows per chunk step
-  __shared__ __attribute__((aligned(16))) bf16 smem[NST * (SA + SB)];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  constexpr int NTILE = SWIGLU ? BNT / 2 : BNT;  // output columns per block
-  const int MT = (a.m_hi - a.m_lo + BMT - 1) / BMT, NTn = (a.N + NTILE - 1) / NTILE, ntiles = MT * NTn;
-  const int per = gridDim.x / 8;
-  const int Lid = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (Lid >= ntiles) return;
-  int tm, tn;
-  {
-    const int gsz = LGM * NTn;
-    const int g = Lid / gsz, r = Lid % gsz;
-    const int fm = g * LGM;
-    const int gm = min(MT - fm, LGM);
-    tm = fm + r % gm;
-    tn = r / gm;
-  }
-  const int m0 = a.m_lo + tm * BMT, n0 = tn * NTILE;
-  const bf16* X = (const bf16*)a.X;
-  const GemmLora& L = a.lora;
-
-  // Each wave fills whole 1 KB LDS slots (8 rows x 128 B); lane `lane` of
-  // chunk i writes LDS row (i*NW + wave)*8 + lane/8, physical 16-byte chunk
-  // lane%8, so it loads the logical chunk that the swizzle maps there.
-  const int row0 = wave * 8 + (lane >> 3);
-  const int kc0 = (lane & 7) ^ swz_bits(row0);  // same for row0 + i * RSTEP
-  // element offsets (32-bit: the launcher keeps M * ldx and N * K below 2^31)
-  // of each chunk's row, to keep the 64-bit pointer pairs out of registers
-  int xoff[ACH];
-#pragma unroll
-  for (int i = 0; i < ACH; ++i) xoff[i] = min(m0 + row0 + i * RSTEP, a.M - 1) * a.ldx + kc0 * 8;
-  int woff[BCH];
-#pragma unroll
-  for (int i = 0; i < BCH; ++i) {
-    const int row = row0 + i * RSTEP;
-    int wrow;
-    if (SWIGLU) {
-      const int sub = row >> 4;
-      wrow = n0 + (sub >> 1) * 16 + (row & 15);
-    } else {
-      wrow = n0 + row;
-    }
-    woff[i] = min(wrow, a.N - 1) * a.K + kc0 * 8;
-  }
-  // SwiGLU: 16-row groups of the B tile alternate gate (W) and up (W2) rows
-  auto wbase = [&](int i) -> const bf16* {
-    if (SWIGLU && (((row0 + i * RSTEP) >> 4) & 1)) return (const bf16*)a.W2;
-    return (const bf16*)a.W;
-  };
-
-  // LoRA steps.  Rows are sorted by task, so the tile's rows form runs of
-  // one task each.  The task ids of the tile's rows arrive with the first
-  // operand DMA (RPL per lane); ballots of the rows that start a run then
-  // list the runs, so a task without rows in the tile (an id absent from the
-  // batch included) costs no step.  A LoRA step is a 64-column K step whose
-  // A tile is U (the slot's columns; rows of other runs zero) and whose B
-  // tile is B_t (zero past the rank).  Without PACK a step serves one run:
-  // ranks <= 32 fill its first 32 columns (a half step; SwiGLU: gate in the
-  // low 32, up in the high 32), a SwiGLU run of a larger rank takes two
-  // steps (gate, then up).  With PACK (every rank <= 16) the step's columns
-  // are cut into P slots, one run each (16 columns; SwiGLU: 16 gate then 16
-  // up), so a tile with many small runs (a few rows each of many tasks)
-  // needs a quarter (a half) of the steps.  Every product a row meets
-  // outside its own slot has a zero operand, so its sum does not depend on
-  // which runs share its step.  A lane's 16-byte chunk of a step row is
-  // fixed for the tile, and so is its slot.  A group's task ids come from
-  // the tile's row tasks (registers); each lane reads its slot's rank and B
-  // pointer from the small per-task tables (cache hits after the first).
-  const int nk = a.K / BK;
-  constexpr int RPL = BMT / 64;                    // tile rows per lane
-  static_assert(BMT % 64 == 0, "rows per lane");
-  const int parts = (SWIGLU && L.max_rank > 32) ? 2 : 1;
-  // chunks (8 columns) per projection of a slot, chunks per slot, slots per step
-  const int hc = PACK ? 2 : L.max_rank > 32 ? 8 : 4;
-  const int cwc = (SWIGLU && parts == 1) ? 2 * hc : hc;
-  constexpr int P = PACK ? (SWIGLU ? 2 : 4) : 1;
-  const int slot = PACK ? kc0 / (SWIGLU ? 4 : 2) : 0;     // this lane's slot
-  const int q = PACK ? kc0 % (SWIGLU ? 4 : 2) : kc0;      // and its chunk within the slot
-  bool live = false;
-  if (L.enabled) {
-    if (SWIGLU) live = L.B[0] != nullptr || L.B[1] != nullptr;
-    else live = L.B[min(n0 / L.slot_width, 2)] != nullptr;
-  }
-  const int lslot = SWIGLU ? 0 : min(n0 / L.slot_width, 2);
-  int rt[RPL];                                     // task of tile row RPL * lane + j
-#pragma unroll
-  for (int j = 0; j < RPL; ++j) rt[j] = live ? L.row_task[min(m0 + RPL * lane + j, a.M - 1)] : 0;
-  uint64_t rstart[RPL];                            // bit l of rstart[j]: row RPL*l + j starts a run
-  int nlora = 0, nsteps = nk;
-  auto first_start_ge = [&](int r) -> int {        // first run start at tile row >= r, else BMT
-    int best = BMT;
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) {
-      const int lmin = r <= j ? 0 : (r - j + RPL - 1) / RPL;
-      if (lmin < 64) {
-        const uint64_t m = rstart[j] & (~0ull << lmin);
-        if (m) best = min(best, RPL * (int)__builtin_ctzll(m) + j);
-      }
-    }
-    return best;
-  };
-  auto task_at = [&](int r) -> int {               // task of tile row r (wave-uniform r)
-    int t = __builtin_amdgcn_readlane(rt[0], r / RPL);
-#pragma unroll
-    for (int j = 1; j < RPL; ++j)
-      if (r % RPL == j) t = __builtin_amdgcn_readlane(rt[j], r / RPL);
-    return t;
-  };
-  // The current step's group (wave-uniform): the tile rows where it starts
-  // and where the next one starts; read when the group's first step is
-  // issued (a SwiGLU group of a rank above 32 takes two steps).
-  int g_start = 0, g_end = 0;
-  int cs = 0, ce = 0, cr = 0;                      // this lane's run: tile rows [cs, ce), rank
-  const bf16* cb = nullptr;                        // and B pointer
-  bool half_next = false;                          // the issued step fills only its first 32 columns
-  auto load_step = [&](int part) {
-    const int start = part == 0 ? g_end : g_start;
-    int b[P + 1];
-    b[0] = start;
-#pragma unroll
-    for (int u = 1; u <= P; ++u) b[u] = b[u - 1] < BMT ? first_start_ge(b[u - 1] + 1) : BMT;
-    int used = 0, mt = -1;
-    cs = ce = BMT;
-#pragma unroll
-    for (int u = 0; u < P; ++u) {
-      const bool has = b[u] < BMT;
-      const int t = has ? task_at(b[u]) : -1;
-      used += has ? cwc : 0;
-      if (u == slot) { cs = b[u]; ce = b[u + 1]; mt = t; }
-    }
-    g_start = start;
-    g_end = b[P];
-    half_next = used <= 4;
-    // the lane's projection: its slot's gate or up half (SwiGLU), else the block's
-    const int proj = SWIGLU ? (parts == 2 ? part : (q >= hc ? 1 : 0)) : lslot;
-    const void* const* tab = proj == 0 ? L.B[0] : proj == 1 ? L.B[1] : L.B[2];
-    cr = 0;
-    cb = nullptr;
-    if (mt >= 0) {
-      cr = min(L.rank[mt], L.max_rank) & ~7;
-      if (tab != nullptr) cb = (const bf16*)tab[mt];
-    }
-  };
-
-  f32x4 acc[FM][FN];
-#pragma unroll
-  for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < FN; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // LDS stage of step e: e & 1 with two, else the caller's j = e % NST
-  auto stage = [&](int e, int j) -> bf16* { return smem + (NST == 2 ? (e & 1) : j) * (SA + SB); };
-  auto issue_bb = [&](int e, int j) {
-    bf16* As = stage(e, j);
-    bf16* Bs = As + SA;
-    const int k0 = e * BK;
-#pragma unroll
-    for (int i = 0; i < ACH; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(X + xoff[i] + k0), (lptr_t)(As + (i * NW + wave) * 512), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < BCH; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(wbase(i) + woff[i] + k0), (lptr_t)(Bs + (i * NW + wave) * 512), 16,
-                                       0, 0);
-  };
-  // A LoRA-step chunk: lanes with data DMA it, the others write zeros into
-  // their own 16-byte LDS slot (a shared zero page read by every CU would
-  // funnel those loads into one L2 line).  The step's wait covers both.
-  auto dma_or_zero = [&](bool on, const bf16* src, bf16* dst) {
-    if (on) __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)dst, 16, 0, 0);
-    else *reinterpret_cast<bf16x8*>(dst + lane * 8) = bf16x8{};
-  };
-  auto issue = [&](int e) {
-    bf16* As = stage(e, e % NST);
-    bf16* Bs = As + SA;
-    if (e < nk) {
-      const int k0 = e * BK;
-#pragma unroll
-      for (int i = 0; i < ACH; ++i)
-        __builtin_amdgcn_global_load_lds((gptr_t)(X + xoff[i] + k0), (lptr_t)(As + (i * NW + wave) * 512), 16, 0, 0);
-#pragma unroll
-      for (int i = 0; i < BCH; ++i)
-        __builtin_amdgcn_global_load_lds((gptr_t)(wbase(i) + woff[i] + k0), (lptr_t)(Bs + (i * NW + wave) * 512), 16,
-                                         0, 0);
-      return;
-    }
-    const int step = e - nk, part = step % parts;
-    if (!(EARLY && step == 0)) load_step(part);
-    const bf16* U = (const bf16*)L.U;
-    // this lane's chunk: projection (SwiGLU: gate or up) and chunk within it
-    int proj = 0, qq = q;
-    if (SWIGLU) {
-      if (parts == 2) proj = part;
-      else { proj = q >= hc ? 1 : 0; qq = q - proj * hc; }
-    }
-    // A: the run's rows of U at the slot's columns.  Only columns the shrink
-    // wrote are read (the rest are zeroed in LDS), so stale workspace bytes
-    // never meet a zero of B.
-    const int ucolA = L.ucol[SWIGLU ? proj : lslot] + qq * 8;
-    const bool colA = qq * 8 < (L.max_rank > 32 ? 64 : 32) && (!SWIGLU || (proj ? L.B[1] : L.B[0]) != nullptr);
-    // with a half step, columns 32..63 are neither loaded nor read
-    const bool skip = half_next && kc0 >= 4;
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      const int row = row0 + i * RSTEP, m = m0 + row;
-      const bool on = colA && row >= cs && row < ce && m < a.M;
-      if (!skip) dma_or_zero(on, U + (int64_t)m * L.ldu + ucolA, As + (i * NW + wave) * 512);
-    }
-    // B: B_t rows of this block's output columns, zero past the rank
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) {
-      const int row = row0 + i * RSTEP;
-      const bf16* src = nullptr;
-      if (SWIGLU) {
-        const int sub = row >> 4, which = sub & 1;
-        const int j = n0 + (sub >> 1) * 16 + (row & 15);
-        if (which == proj && qq * 8 < cr && j < a.N && cb != nullptr) src = cb + (int64_t)j * cr + qq * 8;
-      } else {
-        const int nrow = n0 + row - lslot * L.slot_width;
-        if (qq * 8 < cr && n0 + row < a.N && nrow < L.slot_width && cb != nullptr)
-          src = cb + (int64_t)nrow * cr + qq * 8;
-      }
-      if (!skip) dma_or_zero(src != nullptr, src, Bs + (i * NW + wave) * 512);
-    }
-  };
-  auto compute = [&](int e, int j, bool first_half_only) {
-    const bf16* As = stage(e, j);
-    const bf16* Bs = As + SA;
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      if (kk == 1 && first_half_only) break;
-      const int kc = kk * 4 + (lane >> 4);
-      bf16x8 wf[FN];
-#pragma unroll
-      for (int ni = 0; ni < FN; ++ni) {
-        const int r = wn * TN + ni * 16 + (lane & 15);
-        wf[ni] = *reinterpret_cast<const bf16x8*>(Bs + r * BK + swz(r, kc) * 8);
-      }
-#pragma unroll
-      for (int mi = 0; mi < FM; ++mi) {
-        const int r = wm * TM + mi * 16 + (lane & 15);
-        const bf16x8 xf = *reinterpret_cast<const bf16x8*>(As + r * BK + swz(r, kc) * 8);
-#pragma unroll
-        for (int ni = 0; ni < FN; ++ni) acc[mi][ni] = mfma16(wf[ni], xf, acc[mi][ni]);
-      }
-    }
-  };
-
-  // Waits are explicit: vmcnt(0) makes this wave's LDS-bound loads land, the
-  // raw s_barrier then makes every wave's loads visible.  (A full
-  // __syncthreads would add a fence the loop does not need.)
-  // The backbone K steps run in a loop of their own (its loads are plain
-  // strided tiles), then the LoRA steps; the loop that mixes both kinds of
-  // issue costs the backbone loop about a tenth of its speed.
-  // the residual values this thread adds in the epilogue (its staging order),
-  // so that small tiles do not wait for them at the end
-  constexpr int NOLD = EPI == EPI_RESID && EARLY ? BMT * BNT / 4 / NTH : 1;
-  float4 old[NOLD];
-  if constexpr (EPI == EPI_RESID && EARLY) {
-    constexpr int QR = BNT / 4;
-#pragma unroll
-    for (int i = 0; i < NOLD; ++i) {
-      const int e = tid + NTH * i, m = m0 + e / QR, n = n0 + e % QR * 4;
-      old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (m < a.M && n < a.N) old[i] = *reinterpret_cast<const float4*>((const float*)a.out + (int64_t)m * a.ldo + n);
-    }
-  }
-  issue_bb(0, 0);
-  if constexpr (NST == 2) {
-    __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): step 0 and the tile's row tasks
-    __builtin_amdgcn_s_barrier();
-  } else {
-#pragma unroll
-    for (int e = 1; e < NST - 1; ++e)
-      if (e < nk) issue_bb(e, e);
-  }
-  if (live) {
-    int prev = __shfl_up(rt[RPL - 1], 1, 64);
-    if (lane == 0) prev = -1;
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) {
-      const int before = j == 0 ? prev : rt[j - 1];
-      rstart[j] = __ballot(rt[j] != before);
-    }
-    int nruns = 0;
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) nruns += __builtin_popcountll(rstart[j]);
-    nlora = (nruns + P - 1) / P * parts;
-    nsteps = nk + nlora;
-    if (EARLY) load_step(0);           // the first LoRA step's rank and B pointer arrive during the K loop
-  }
-  if constexpr (NST == 2) {
-    if (nk < 2) __builtin_amdgcn_s_waitcnt(0xF70);   // no backbone step covers them
-    // (small tiles also wait for their fragment reads before the barrier: what
-    // the compiler leaves of a step's reads until after it would race with
-    // the zeros that the first LoRA step writes, its tables already there;
-    // the large tiles' next write to the stage is a load's round trip away)
-    for (int e = 0; e + 1 < nk; ++e) {
-      issue_bb(e + 1, 0);     // the other stage: every wave left it at the last barrier
-      compute(e, 0, false);
-      __builtin_amdgcn_s_waitcnt(EARLY ? 0x0070 : 0xF70);
-      __builtin_amdgcn_s_barrier();
-    }
-  } else {
-    // NST - 1 steps in flight: step e has landed once at most NST - 2 later
-    // ones are outstanding; the barrier also frees the stage of step e - 1.
-    // The stages are constants of the unrolled loop, so the compiler can tell
-    // the one being read from those being filled.
-    for (int e0 = 0; e0 + 1 < nk; e0 += NST) {
-#pragma unroll
-      for (int j = 0; j < NST; ++j) {
-        const int e = e0 + j;
-        if (e + 1 >= nk) break;
-        wait_steps<ACH + BCH, NST - 2>(nk - 1 - e);
-        __builtin_amdgcn_s_barrier();
-        if (e + NST - 1 < nk) issue_bb(e + NST - 1, (j + NST - 1) % NST);
-        compute(e, j, false);
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0x0070);  // step nk - 1 and the row tasks
-    __builtin_amdgcn_s_barrier();
-  }
-  bool half_cur = false;                           // step e fills only its first 32 columns
-  for (int e = nk - 1; e < nsteps; ++e) {
-    if (e + 1 < nsteps) issue(e + 1);
-    compute(e, e % NST, e >= nk && half_cur);
-    half_cur = half_next;
-    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): DMA and zero writes done
-    __builtin_amdgcn_s_barrier();
-  }
-  // whole rows through LDS (16 B per lane) for the bf16 outputs and for the
-  // fp32 residual of tiles narrower than 256 columns; the 256-column
-  // residual tile writes from registers (its staged form spills)
-  if (EPI != EPI_RESID || BNT < 256)
-    epilogue_lds<EPI, SWIGLU, BMT, BNT, WM, NST, FM, FN>(a, reinterpret_cast<char*>(smem), m0, n0, wm, wn, lane, tid,
-                                                         acc, old);
-  else
-    epilogue_frags<EPI, SWIGLU, FM, FN>(a, m0 + wm * TM, n0, wn * TN, lane, acc);
-}
-
 template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
-  gemm_bf16_tile<EPI, SWIGLU, BMT, BNT, PACK, 4, 2>(a);
+  constexpr int WM = 4, NST = 2;
+#include "gemm_tile.inc"
 }
 
 // The same tile for products with too few 256-row tiles to fill the chip: 4
@@ -752,7 +405,8 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_large_kernel(GemmArgs a) {
 // slower or equal.  K steps and their order are those of the large tiles.
 template <int EPI, bool SWIGLU, int BMT, int BNT, bool PACK>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_mid_kernel(GemmArgs a) {
-  gemm_bf16_tile<EPI, SWIGLU, BMT, BNT, PACK, 2, BMT == 64 ? 4 : 2>(a);
+  constexpr int WM = 2, NST = BMT == 64 ? 4 : 2;
+#include "gemm_tile.inc"
 }
 
 // ---------------------------------------------------------------------------
