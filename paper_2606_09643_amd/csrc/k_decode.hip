@@ -487,7 +487,8 @@ Walk skinny_walk(int M, int N, int K, int split_bn, int nsplit) {
   if (M <= 128 || nsplit < 2) return best;
   const double nkt = K / SBK;
   const double step = split_bn == 128 ? 1.2 : split_bn == 192 ? 1.55 : 1.9;
-  double cost = (M + 255) / 256 * (nkt / nsplit * step + 7.0) + (nsplit - 1) * 4e-6 * M * N / 6.6;
+  const int blocks = (N + split_bn - 1) / split_bn * nsplit * ((M + 255) / 256);
+  double cost = (blocks + 255) / 256 * (nkt / nsplit * step + 7.0) + (nsplit - 1) * 4e-6 * M * N / 6.6;
   constexpr struct { int bm, bn; double step; } cand[4] = {
       {128, 128, 0.62}, {128, 192, 0.78}, {192, 192, 1.0}, {256, 192, 1.32}};
   for (const auto& c : cand) {
