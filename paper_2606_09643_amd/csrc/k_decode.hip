@@ -57,13 +57,17 @@ __device__ __forceinline__ void shrink_split_rows(const Plan& pl, const ShrinkSp
     for (int s = 0; s < NSUB; ++s) acc[pp][s] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (rank > 0 && m0 < r1) {
     const bf16* xrow = (const bf16*)a.X + (int64_t)min(m, r1 - 1) * a.ldx + 8 * (lane >> 4);
-    const bf16* arow[NP][NSUB];
+    // told that the factors lie in global memory: with a projection known only
+    // at run time the compiler loses track of it and loads them flat
+    typedef const bf16 __attribute__((address_space(1)))* growp;
+    typedef const bf16x8 __attribute__((address_space(1)))* gfragp;
+    growp arow[NP][NSUB];
     bool on[NSUB];
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) on[s] = s * 16 + (lane & 15) < rank;
 #pragma unroll
     for (int pp = 0; pp < NP; ++pp) {
-      const bf16* At = (const bf16*)a.A[pp0 + pp][t];
+      const growp At = (growp)((const void* const __attribute__((address_space(1)))*)a.A[pp0 + pp])[t];
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
         arow[pp][s] = At + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + 8 * (lane >> 4);
@@ -75,7 +79,7 @@ __device__ __forceinline__ void shrink_split_rows(const Plan& pl, const ShrinkSp
       for (int pp = 0; pp < NP; ++pp)
 #pragma unroll
         for (int s = 0; s < NSUB; ++s) {
-          bf16x8 af = *reinterpret_cast<const bf16x8*>(arow[pp][s] + k);
+          bf16x8 af = *(gfragp)(arow[pp][s] + k);
           if (!on[s]) af = bf16x8{};
           acc[pp][s] = mfma16(af, xf, acc[pp][s]);
         }
