@@ -1019,6 +1019,10 @@ __global__ __launch_bounds__(256) void attn_decode_bf16_kernel(Plan pl, const bf
       step(1, k0 + STEP);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // the last step's prefetch is not used: its registers are taken until it has landed
+#pragma unroll
+    for (int u = 0; u < UNR; ++u)
+      asm volatile("" ::"v"(kb[0][u]), "v"(vb[0][u]), "v"(kb[1][u]), "v"(vb[1][u]));
   }
   if (sub == 0) { sm[grp] = m_run; sl[grp] = l_run; }
 #pragma unroll
