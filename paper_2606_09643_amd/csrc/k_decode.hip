@@ -345,6 +345,7 @@ __global__ __launch_bounds__(256 * NWN) void gemm_skinny_kernel(SkinnyArgs a) {
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
   __shared__ float Us[3 * VFM_MAX_RANK], red[256];
+  __shared__ __attribute__((aligned(16))) float cols[4][256];
   __shared__ float rcs[64], rsn[64];          // the row's rotary angles (head_dim / 2 <= 64)
   // Block b takes (column block, row) number (b % 8) * per + b / 8, rows
   // fastest: consecutive blocks of one XCD (one L2) take consecutive rows of
@@ -374,20 +375,19 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
     __syncthreads();
   }
   const int n = (cb * 256 + threadIdx.x) * 4;
-  if (n >= a.N) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = cb * 1024 + wave * 256;
+  if (first >= a.N) return;                   // wave-uniform; lanes past N leave after the LoRA sums
   const bool swiglu = a.epi == EPI_SWIGLU;
   const int nz = swiglu ? 2 * a.N : a.N;   // columns of Z
   const int64_t zs = (int64_t)a.M * nz;
-  const float* z = a.Z + (int64_t)m * nz + n;
-  float4 v = sum_slices(z, zs, a.nslices);
+  const float* z = a.Z + (int64_t)m * nz + min(n, a.N - 4);
+  float4 v = sum_slices(z, zs, a.nslices), u = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (swiglu) u = sum_slices(z + a.N, zs, a.nslices);
   if (a.lora.enabled) {
-    if (swiglu) {
-      add4(v, fin_lora_delta(a.lora, bp, r, 0, n, Us));
-    } else {
-      const int slot = min(n / a.lora.slot_width, 2);
-      add4(v, fin_lora_delta(a.lora, bp, r, slot, n - slot * a.lora.slot_width, Us));
-    }
+    add4(v, fin_lora_wave(a.lora, bp, r, swiglu ? 0 : -1, first, a.N, Us, cols[wave]));
+    if (swiglu) add4(u, fin_lora_wave(a.lora, bp, r, 1, first, a.N, Us, cols[wave]));
   }
+  if (n >= a.N) return;
   if (a.bias && !swiglu) {
     const bf16x4 bv = *reinterpret_cast<const bf16x4*>((const bf16*)a.bias + n);
     v.x += (float)bv[0]; v.y += (float)bv[1]; v.z += (float)bv[2]; v.w += (float)bv[3];
@@ -421,12 +421,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
     v = make_float4(x4[0], x4[1], x4[2], x4[3]);
   }
   const float g4[4] = {v.x, v.y, v.z, v.w};
-  float u4[4] = {0.f, 0.f, 0.f, 0.f};
-  if (swiglu) {
-    float4 u = sum_slices(z + a.N, zs, a.nslices);
-    if (a.lora.enabled) add4(u, fin_lora_delta(a.lora, bp, r, 1, n, Us));
-    u4[0] = u.x; u4[1] = u.y; u4[2] = u.z; u4[3] = u.w;
-  }
+  const float u4[4] = {u.x, u.y, u.z, u.w};
   bf16x4 o;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {

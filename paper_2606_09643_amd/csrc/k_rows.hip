@@ -186,6 +186,7 @@ __global__ __launch_bounds__(NT) void finalize_norm_kernel(FinalizeArgs a, const
                                                             T* __restrict__ h) {
   __shared__ float red[2][NT / 64];
   __shared__ float Us[3 * VFM_MAX_RANK], ured[NT];
+  __shared__ __attribute__((aligned(16))) float cols[NT / 64][256];
   // block b takes row (b % 8) * per + b / 8: consecutive rows (often one
   // task's) run on one XCD, so the task's B rows come from that XCD's L2
   const int per = gridDim.x / 8;
@@ -206,12 +207,13 @@ __global__ __launch_bounds__(NT) void finalize_norm_kernel(FinalizeArgs a, const
   for (int i = 0; i < MAXC; ++i) {
     const int c = tid + NT * i;
     v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 s4 = v[i];
+    if (c < nch) s4 = sum_slices(a.Z + (int64_t)row * a.N + 4 * c, zs, a.nslices);
+    if (a.lora.enabled) {
+      const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      add4(s4, fin_lora_wave(a.lora, bp, r, -1, 256 * wave + 4 * NT * i, a.N, Us, cols[wave]));
+    }
     if (c < nch) {
-      float4 s4 = sum_slices(a.Z + (int64_t)row * a.N + 4 * c, zs, a.nslices);
-      if (a.lora.enabled) {
-        const int slot = min(4 * c / a.lora.slot_width, 2);
-        add4(s4, fin_lora_delta(a.lora, bp, r, slot, 4 * c - slot * a.lora.slot_width, Us));
-      }
       if (a.bias) {
         const bf16x4 bv = *reinterpret_cast<const bf16x4*>((const bf16*)a.bias + 4 * c);
         s4.x += (float)bv[0]; s4.y += (float)bv[1]; s4.z += (float)bv[2]; s4.w += (float)bv[3];

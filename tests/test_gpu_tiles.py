@@ -209,3 +209,17 @@ def test_walked_splits_same_as_split_launch(lens):
     whole = _rows_of(w, model, [2] + [0, 1][:len(lens)], [100] + [n - 100 if i == 0 else n for i, n in enumerate(lens)],
                      [5, 6, 7][:len(lens) + 1])[0]
     assert torch.equal(alone, whole)
+
+
+@pytest.mark.parametrize("idx,d,hd,d_ff", [(3, 1088, 64, 2880), (4, 1344, 64, 1856), (4, 2048, 128, 5504)])
+@pytest.mark.parametrize("ranks", [[16, 8, 24, 0, 16], [64, 16, 32, 48, 8]])
+def test_finalize_lora_columns(idx, d, hd, d_ff, ranks):
+    """The finalize's LoRA difference: every rank, rows of the factors loaded by
+    whole waves and by lanes (ranks that do not divide a wave, slots that end
+    inside one), a last wave without all of its columns."""
+    w = wl.WORKLOADS[idx].replace(d=d, n_heads=d // hd, head_dim=hd, d_ff=d_ff, n_tasks=5,
+                                  lora_targets=wl.PROJ if idx == 4 else ("q", "v", "o", "up", "down"))
+    lens = [1, 40, 3, 7, 30]
+    log(f"finalize columns {w.name} d={d} ranks={ranks}")
+    out = _layer_case(w, [4, 2, 0, 3, 1], lens, ranks, b_std=0.05)
+    _check_layer(w, out[0], out[1], out[2], out[3], range(len(lens)))
