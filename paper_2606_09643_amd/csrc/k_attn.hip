@@ -454,7 +454,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CAUSAL ? 3 
 // resident the softmax is one pass (max, exp, sum) with no rescaling.  Keys
 // are padded to a multiple of 32 with zeros and masked.
 // ---------------------------------------------------------------------------
-template <int DH, bool CAUSAL, int NKS, int NW = 4>
+template <int DH, bool CAUSAL, int NKS, int NW, int NZ>
 __global__ __launch_bounds__(64 * NW) void attn_short_bf16_kernel(Plan pl, const bf16* __restrict__ qkv,
                                                               int d, bf16* __restrict__ out,
                                                               float scale_log2, int mixed) {
@@ -466,7 +466,8 @@ __global__ __launch_bounds__(64 * NW) void attn_short_bf16_kernel(Plan pl, const
   const int p = blockIdx.x, h = blockIdx.y;
   const int R = pl.cu_seqlens[p];
   const int L = pl.cu_seqlens[p + 1] - R;
-  if (L > LMAX || blockIdx.z * NW * 16 >= L) return;   // block-uniform: a flash-kernel request, or no group left
+  const int z = NZ > 1 ? blockIdx.z : 0;
+  if (L > LMAX || z * NW * 16 >= L) return;     // block-uniform: a flash-kernel request, or no group left
   if (mixed && pl.ctx[p] > 0) return;           // block-uniform: the cache-reading kernels'
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4;
   const int64_t ld = 3 * (int64_t)d;
@@ -506,8 +507,9 @@ __global__ __launch_bounds__(64 * NW) void attn_short_bf16_kernel(Plan pl, const
     for (int s2 = 0; s2 < DH / 32; ++s2) qf[s2] = *reinterpret_cast<const bf16x8*>(qrow + s2 * 32);
   };
   bf16x8 qnext[DH / 32];
-  // the 16-query groups go round the waves of gridDim.z blocks
-  const int qg0 = blockIdx.z * NW + wave, qstep = NW * gridDim.z;
+  // the 16-query groups go round the waves of NZ blocks
+  constexpr int qstep = NW * NZ;
+  const int qg0 = z * NW + wave;
   if (qg0 * 16 < L) load_q(qg0, qnext);
   for (int qg = qg0; qg * 16 < L; qg += qstep) {
     const int qi = qg * 16 + (lane & 15);
@@ -1148,11 +1150,13 @@ hipError_t launch_attention(int dtype, const Plan& pl, const vfm_cfg& c, const v
       // a second block per (request, head) where those leave half of the CUs
       // without one: its waves then take one query group each instead of two
       // (one 197-token request of 12 heads: 10.2 -> 7.1 us)
-      dim3 g2(pl.n_req, H, pl.max_short > 128 && pl.n_req * H <= 128 ? 2 : 1);
+      const int nz = pl.max_short > 128 && pl.n_req * H <= 128 ? 2 : 1;
+      dim3 g2(pl.n_req, H, nz);
       const int nks = ((pl.max_short + 31) / 32) * 2;   // 16-key sub-tiles, even
-#define SHORT(D_, C_, N_)                                                                           \
-  hipLaunchKernelGGL((attn_short_bf16_kernel<D_, C_, N_, 8>), g2, dim3(512), 0, s, pl, (const bf16*)qkv, \
+#define SHORT_Z(D_, C_, N_, Z_)                                                                     \
+  hipLaunchKernelGGL((attn_short_bf16_kernel<D_, C_, N_, 8, Z_>), g2, dim3(512), 0, s, pl, (const bf16*)qkv, \
                      d, (bf16*)out, scale_log2, (int)mixed)
+#define SHORT(D_, C_, N_) do { if (N_ > 8 && nz == 2) SHORT_Z(D_, C_, N_, (N_ > 8 ? 2 : 1)); else SHORT_Z(D_, C_, N_, 1); } while (0)
 #define SHORT_N(D_, C_)                                            \
   switch (nks) {                                                   \
     case 2: SHORT(D_, C_, 2); break;   case 4: SHORT(D_, C_, 4); break;   \
@@ -1163,6 +1167,7 @@ hipError_t launch_attention(int dtype, const Plan& pl, const vfm_cfg& c, const v
       if (causal) { SHORT_N(64, true); } else { SHORT_N(64, false); }
 #undef SHORT_N
 #undef SHORT
+#undef SHORT_Z
     }
     if (dtype == VFM_BF16 && (short_rows == 0 || pl.n_long > 0)) {
       // requests longer than short_rows (the others return)
