@@ -483,7 +483,10 @@ void skinny_shape(int N, int K, int* bn, int* nsplit) {
 struct Walk { int bm, bn; };
 Walk skinny_walk(int M, int N, int K, int split_bn, int nsplit) {
   Walk best = {0, 0};
-  if (M <= 128 || nsplit < 2) return best;
+  // one row tile of the split launch: its weights are read once, and the walk
+  // was slower (130 / 192 / 256 rows of 7B decode 302 / 345 / 393 us a layer
+  // walked, 291 / 338 / 387 split)
+  if (M <= 256 || nsplit < 2) return best;
   const double nkt = K / SBK;
   const double step = split_bn == 128 ? 1.2 : split_bn == 192 ? 1.55 : 1.9;
   const int blocks = (N + split_bn - 1) / split_bn * nsplit * ((M + 255) / 256);
