@@ -7,6 +7,7 @@ cross-compiles to AMD assembly).
   immediately before a `ds_read_b128` (the compiler inserts one whenever it
   cannot tell the two LDS stages apart, which serialises load and compute).
 * No packed fp32 arithmetic is emitted.
+* No wave meets a barrier with LDS accesses of its own unfinished.
 """
 import os
 import re
@@ -171,3 +172,77 @@ def test_untracked_loads_not_touched_before_their_wait(all_asm):
                     else:
                         inflight.append(None)
     assert checked > 0
+
+
+def _flow(body):
+    """(basic blocks as instruction lists, {label: block}) of a kernel's text."""
+    blocks, labels = [[]], {}
+    for raw in body.splitlines():
+        l = raw.split(";")[0].strip()
+        if l.startswith(".L") and l.endswith(":"):
+            if blocks[-1]:
+                blocks.append([])
+            labels[l[:-1]] = len(blocks) - 1
+        elif l and not l.startswith(".") and not l.endswith(":"):
+            blocks[-1].append(l)
+            if re.match(r"s_(c?branch|endpgm)", l):
+                blocks.append([])
+    return blocks, labels
+
+
+def _unfinished_at_barriers(body):
+    """The LDS accesses (r / w) that a wave may still have in flight at each
+    s_barrier, over every path: a walk of the control flow with the lgkmcnt
+    operations in issue order.  lgkmcnt(N) retires all but the last N, except
+    beside scalar loads (s), which complete in any order."""
+    blocks, labels = _flow(body)
+    rank = {"r": 3, "w": 2, "s": 1}
+
+    def merge(a, b):                                      # the longer, the worse of each, from the newest back
+        long, short = (a, b) if len(a) >= len(b) else (b, a)
+        tail = [max(x, y, key=rank.get) for x, y in zip(long[len(long) - len(short):], short)]
+        return long[:len(long) - len(short)] + tuple(tail)
+
+    entry, todo, found = {0: ()}, [0], {}
+    while todo:
+        i = todo.pop()
+        state, succ, falls = entry[i], [], True
+        for j, l in enumerate(blocks[i]):
+            mnem, _, rest = l.partition(" ")
+            if mnem == "s_waitcnt" and "lgkmcnt" in rest:
+                n = int(re.search(r"lgkmcnt\((\d+)\)", rest).group(1))
+                state = () if n == 0 else state if "s" in state else state[-n:]
+            elif mnem == "s_barrier":
+                found[i, j] = merge(found.get((i, j), ()), state)
+            elif mnem.startswith("ds_read") or mnem.startswith("flat_load"):
+                state = (state + ("r",))[-64:]
+            elif mnem.startswith(("ds_", "flat_")):
+                state = (state + ("w",))[-64:]
+            elif re.match(r"s_(buffer_)?load", mnem):
+                state = (state + ("s",))[-64:]
+            elif re.match(r"s_c?branch", mnem):
+                succ.append(labels[rest.strip()])
+                falls = mnem != "s_branch"
+            elif mnem == "s_endpgm":
+                falls = False
+        if falls and i + 1 < len(blocks):
+            succ.append(i + 1)
+        for k in succ:
+            new = merge(entry[k], state) if k in entry else state
+            if entry.get(k) != new:
+                entry[k] = new
+                todo.append(k)
+    return [set(v) & {"r", "w"} for v in found.values()]
+
+
+def test_lds_accesses_finish_before_barriers(all_asm):
+    """A wave's LDS reads and writes have finished when it meets a barrier:
+    after it another wave may fill the stage that they touch (the GEMMs' raw
+    barriers carry no wait of their own)."""
+    barriers = 0
+    for f, asm in all_asm.items():
+        for m in re.finditer(r"^(_Z\S+):\s*(?:;.*)?$", asm, re.M):
+            found = _unfinished_at_barriers(asm[m.end():asm.find(".Lfunc_end", m.end())])
+            barriers += len(found)
+            assert not any(found), f"{f}: {m.group(1)} passes a barrier with {found} unfinished"
+    assert barriers > 100
