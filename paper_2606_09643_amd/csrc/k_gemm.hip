@@ -52,8 +52,9 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 typedef const void __attribute__((address_space(1)))* gptr_t;
 typedef void __attribute__((address_space(3)))* lptr_t;
 
-// Fused per-task LoRA expand for one wave's FM x FN fragment grid (shared by
-// both bf16 kernels).  wrow0 / wcol0: the wave's first row / first B-tile row.
+// Per-task LoRA expand for one wave's FM x FN fragment grid, a task at a time,
+// each task's sums going to its own rows only.  wrow0 / wcol0: the wave's
+// first row / first B-tile row.
 template <int FM, int FN, bool SWIGLU>
 __device__ __forceinline__ void lora_expand_frags(const GemmArgs& a, int m0, int BMrows, int wrow0,
                                                   int n0, int wcol0, int lane,
@@ -66,7 +67,7 @@ __device__ __forceinline__ void lora_expand_frags(const GemmArgs& a, int m0, int
     const int r = min(L.rank[t], L.max_rank) & ~7;
     if (r <= 0) continue;
     const int s0 = L.seg_row[t], s1 = L.seg_row[t + 1];
-    if (s1 <= wrow0 || s0 >= wrow0 + FM * 16) continue;
+    if (s0 >= s1 || s1 <= wrow0 || s0 >= wrow0 + FM * 16) continue;   // no rows here
     for (int kk = 0; kk < r; kk += 32) {
       const int kof = kk + 8 * (lane >> 4);
       const bool kin = kof < r;
@@ -91,19 +92,53 @@ __device__ __forceinline__ void lora_expand_frags(const GemmArgs& a, int m0, int
           nlim = L.slot_width;
         }
         if (L.B[slot] == nullptr) continue;
-        const bf16* Bt = (const bf16*)L.B[slot][t];
+        // a pointer from the table: read as global memory, not through flat addressing
+        typedef const bf16 __attribute__((address_space(1)))* growp;
+        const growp Bt = (growp)L.B[slot][t];
         bf16x8 wf = {};
-        if (kin && nrow < nlim) wf = *reinterpret_cast<const bf16x8*>(Bt + (int64_t)nrow * r + kof);
+        if (kin && nrow < nlim) wf = *(const bf16x8 __attribute__((address_space(1)))*)(Bt + (int64_t)nrow * r + kof);
 #pragma unroll
         for (int mi = 0; mi < FM; ++mi) {
           const int m = wrow0 + mi * 16 + (lane & 15);
+          const bool own = m >= s0 && m < s1;
           bf16x8 x = {};
-          if (m >= s0 && m < s1 && m < a.M)
-            x = *reinterpret_cast<const bf16x8*>(U + (int64_t)m * L.ldu + L.ucol[slot] + kof);
-          acc[mi][ni] = mfma16(wf, x, acc[mi][ni]);
+          if (own && m < a.M) x = *reinterpret_cast<const bf16x8*>(U + (int64_t)m * L.ldu + L.ucol[slot] + kof);
+          const f32x4 v = mfma16(wf, x, acc[mi][ni]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[mi][ni][e] = own ? v[e] : acc[mi][ni][e];
         }
       }
     }
+  }
+}
+
+// The backbone sums of one wave's fragment grid, operands read straight from
+// global memory: the K steps of the tile kernels in their order.
+template <int FM, int FN, bool SWIGLU>
+__device__ __forceinline__ void backbone_frags(const GemmArgs& a, int wrow0, int n0, int wcol0, int lane,
+                                               f32x4 (&acc)[FM][FN]) {
+#pragma unroll
+  for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < FN; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int x = lane & 15;
+#pragma unroll 1
+  for (int k = 8 * (lane >> 4); k < a.K; k += 32) {
+    bf16x8 wf[FN], xf[FM];
+#pragma unroll
+    for (int ni = 0; ni < FN; ++ni) {
+      const int sub = wcol0 / 16 + ni;               // SwiGLU: gate and up rows alternate by 16
+      const int row = SWIGLU ? n0 + (sub >> 1) * 16 + x : n0 + wcol0 + ni * 16 + x;
+      const bf16* W = (const bf16*)(SWIGLU && (sub & 1) ? a.W2 : a.W);
+      wf[ni] = *reinterpret_cast<const bf16x8*>(W + (int64_t)min(row, a.N - 1) * a.K + k);
+    }
+#pragma unroll
+    for (int mi = 0; mi < FM; ++mi)
+      xf[mi] = *reinterpret_cast<const bf16x8*>((const bf16*)a.X + (int64_t)min(wrow0 + mi * 16 + x, a.M - 1) * a.ldx + k);
+#pragma unroll
+    for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < FN; ++ni) acc[mi][ni] = mfma16(wf[ni], xf[mi], acc[mi][ni]);
   }
 }
 

@@ -95,6 +95,28 @@ def test_small_batch_rows_same_in_any_tile(idx, d, d_ff, ranks, lens):
         assert torch.equal(alone, whole[i]), f"request {i} of {lens}"
 
 
+@pytest.mark.parametrize("idx,d,d_ff,ranks", [(2, 768, 3072, [16, 8, 16, 0, 8]), (3, 1024, 2816, [64, 8, 16, 0, 40]),
+                                              (4, 1024, 960, [16, 16, 8, 0, 8]), (4, 1024, 960, [32, 8, 32, 16, 24]),
+                                              (4, 1024, 960, [48, 64, 8, 0, 16]), (4, 2048, 5504, [16, 8, 16, 0, 8])])
+@pytest.mark.parametrize("lens", [[1, 2, 1, 3, 1], [70, 30, 1, 40, 200]])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_broken_adapter_stays_with_its_task(idx, d, d_ff, ranks, lens, bad):
+    """Small batches: a task whose expand factors hold an infinity or a NaN
+    spoils its own requests only; every other request keeps its bits, in tiles
+    that hold rows of both, LoRA steps of one run and of several."""
+    w = wl.WORKLOADS[idx].replace(d=d, n_heads=d // 128 if idx == 4 else d // 64, d_ff=d_ff, n_tasks=5,
+                                  lora_targets=wl.PROJ if idx == 4 else ("q", "k", "v", "o", "up", "down"))
+    model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=0.05)
+    log(f"broken adapter {w.name} d={d} lens={lens} ranks={ranks} {bad}")
+    whole = _rows_of(w, model, [3, 0, 2, 1, 4], lens, [5, 6, 7, 8, 9])
+    for p, B_t in model.adapters[0].B.items():
+        B_t[2, ::7] = bad
+    got = _rows_of(w, model, [3, 0, 2, 1, 4], lens, [5, 6, 7, 8, 9])
+    assert not got[2].isfinite().any()
+    for i in (0, 1, 3, 4):
+        assert whole[i].isfinite().all() and torch.equal(whole[i], got[i]), f"request {i}"
+
+
 @pytest.mark.parametrize("idx,more", [(2, [1024 - 197]), (2, [5000]), (3, [1000]), (3, [9000])])
 def test_large_batch_rows_same_in_any_tile(idx, more):
     """From the threshold on: the same bits from the 64- and 128-row tiles of
