@@ -359,7 +359,12 @@ __device__ __forceinline__ void head_dots(const bf16* wrow, const bf16* const (&
   }
 }
 
-template <bool HID>
+// BYREQ: the table has more tasks than the batch has requests.  A block is
+// then found by plan position, and a task's blocks are those of its first
+// request, so the grid grows with the batch and not with the table: pooling
+// and head of one request among 8192 tasks of 1000 outputs 316 us with a block
+// per task and 16 outputs, 18.8 us so (among 16 tasks: 17.5).
+template <bool HID, bool BYREQ>
 __global__ __launch_bounds__(64 * HEAD_WAVES) void heads_bf16_kernel(Plan pl, const bf16* __restrict__ pooled,
                                                                     int d, vfm_head_table h, int nchunk,
                                                                     bf16* __restrict__ hid,
@@ -367,7 +372,9 @@ __global__ __launch_bounds__(64 * HEAD_WAVES) void heads_bf16_kernel(Plan pl, co
   __shared__ f32x4 red[HEAD_WAVES][HEAD_NG][64];
   // a task's blocks follow each other, in task order: the tasks of skewed
   // mixes that own most requests (the first ids under a Zipf law) start first
-  const int t = blockIdx.x / nchunk, chunk = blockIdx.x % nchunk;
+  const int i = blockIdx.x / nchunk, chunk = blockIdx.x % nchunk;
+  const int t = BYREQ ? pl.task[i] : i;
+  if (BYREQ && i > 0 && pl.task[i - 1] == t) return;   // block-uniform: not the task's first request
   // every table entry is requested before the first is used
   const int p0 = pl.seg_req[t], p1 = pl.seg_req[t + 1];
   const void* const w1 = h.W1 != nullptr ? h.W1[t] : nullptr;
@@ -559,23 +566,25 @@ hipError_t launch_heads(int dtype, const Plan& pl, const void* pooled, int d,
   char* hid = (char*)pooled + (((size_t)pl.n_req * d * es + 255) & ~(size_t)255);
   // blocks per task: one per 16 outputs, fewer (each then takes several
   // chunks) only where tasks x chunks would outgrow a grid
-  auto chunks = [&](int n) { return std::max(1, std::min((n + 15) / 16, (1 << 22) / h.n_tasks)); };
+  const bool byreq = pl.n_req < h.n_tasks;
+  const int nt = byreq ? pl.n_req : h.n_tasks;
+  auto chunks = [&](int n) { return std::max(1, std::min((n + 15) / 16, (1 << 22) / nt)); };
   const int nh = chunks(h.hidden), no = chunks(h.max_out);
+#define HEADS_BF16(HID_, BY_, N_)                                                                        \
+  hipLaunchKernelGGL((heads_bf16_kernel<HID_, BY_>), dim3(nt * N_), dim3(64 * HEAD_WAVES), 0, s, pl, \
+                     (const bf16*)pooled, d, h, N_, (bf16*)hid, out)
   if (h.W1 && h.hidden > 0) {
-    if (dtype == VFM_BF16)
-      hipLaunchKernelGGL((heads_bf16_kernel<true>), dim3(h.n_tasks * nh), dim3(64 * HEAD_WAVES), 0, s, pl,
-                         (const bf16*)pooled, d, h, nh, (bf16*)hid, out);
+    if (dtype == VFM_BF16) { if (byreq) HEADS_BF16(true, true, nh); else HEADS_BF16(true, false, nh); }
     else
       hipLaunchKernelGGL((heads_f32_kernel<true>), dim3(h.n_tasks, (h.hidden + 63) / 64), dim3(256), 0, s, pl,
                          (const float*)pooled, d, h, (float*)hid, out);
   }
   if (h.max_out == 0) return hipGetLastError();
-  if (dtype == VFM_BF16)
-    hipLaunchKernelGGL((heads_bf16_kernel<false>), dim3(h.n_tasks * no), dim3(64 * HEAD_WAVES), 0, s, pl,
-                       (const bf16*)pooled, d, h, no, (bf16*)hid, out);
+  if (dtype == VFM_BF16) { if (byreq) HEADS_BF16(false, true, no); else HEADS_BF16(false, false, no); }
   else
     hipLaunchKernelGGL((heads_f32_kernel<false>), dim3(h.n_tasks, (h.max_out + 63) / 64), dim3(256), 0, s, pl,
                        (const float*)pooled, d, h, (float*)hid, out);
+#undef HEADS_BF16
   return hipGetLastError();
 }
 

@@ -61,6 +61,83 @@ def test_heads_output_and_request_remainders(idx, d, pool, hidden):
     assert err < tol(w)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pool", ["mean", "first"])
+def test_heads_of_a_table_larger_than_the_batch(pool, dtype):
+    """More tasks than requests: first and last ids, neighbouring ones, several
+    requests of one task, MLP and linear heads, a head without outputs."""
+    w = wl.WORKLOADS[2].replace(n_tasks=2500, pool=pool, dtype=dtype)
+    hidden, ids, counts = 64, [0, 1, 700, 701, 1024, 2499], [3, 1, 1, 18, 2, 1]
+    n_out = np.zeros(w.n_tasks, np.int32)
+    n_out[ids] = [17, 1, 250, 33, 0, 1000]
+    r = np.random.default_rng(5)
+    task = r.permutation(np.repeat(ids, counts)).astype(np.int32)
+    batch = wl.Batch(task, r.integers(1, 4, size=len(task)).astype(np.int32), None)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    t_ = lambda *shape, std: (torch.randn(*shape, generator=g, device="cuda") * std).to(w.torch_dtype)  # noqa: E731
+    Ws, W1, b1 = [None] * w.n_tasks, [None] * w.n_tasks, [None] * w.n_tasks
+    for t in ids:
+        if t % 2:
+            W1[t], b1[t] = t_(hidden, w.d, std=w.d ** -0.5), t_(hidden, std=0.1)
+        if n_out[t]:
+            k = hidden if t % 2 else w.d
+            Ws[t] = t_(int(n_out[t]), k, std=k ** -0.5)
+    tab = B.HeadTable(n_out, Ws, [None] * w.n_tasks, R._POOL[pool], W1s=W1, b1s=b1, hidden=hidden)
+    final, pb = wl.final_norm(w, "cuda"), B.Batch(batch.task_id, batch.seq_len, w.n_tasks, n_out=n_out)
+    rows, cfg = seeded_rows(pb.T, w.d, 11), R.cfg_for(w)
+    x = torch.empty(pb.T, w.d, device="cuda")
+    set_rows(x, rows)
+    ws = torch.empty(B.vfm_workspace_size(cfg, pb.c), dtype=torch.uint8, device="cuda")
+    out = torch.full((pb.total_outputs,), float("nan"), device="cuda")
+    log(f"heads of 2500 tasks pool={pool} {dtype}")
+    B.vfm_head_forward(cfg, final["w"], final["b"], tab.c, pb.c, x, out, ws)
+    got = out.cpu().numpy()
+    pl, spec = oracle_plan(w, batch, n_out), spec_of(w)
+    cu, off = pl["cu_seqlens"], pl["logit_off"]
+    ref = np.empty(len(got))
+    for p, i in enumerate(pl["order"]):
+        t = int(pl["task"][p])
+        v = O.pool(O.final(spec, np64(final["w"]), np64(final["b"]), rows[int(cu[p]):int(cu[p + 1])]), pool)
+        z = np.zeros(int(n_out[t]))
+        if n_out[t]:
+            ref[off[i]:off[i + 1]] = (O.head_mlp(v, np64(W1[t]), np64(b1[t]), np64(Ws[t]), z) if t % 2
+                                      else O.head(v, np64(Ws[t]), z))
+    err = np.abs(got - ref).max() / np.abs(ref).max()
+    log(f"  max rel err {err:.3e}")
+    assert err < tol(w)
+
+
+def _us(run, n=20):
+    """Median time of run() on the GPU, microseconds."""
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2 * n)]
+    for _ in range(3):
+        run()
+    for i in range(n):
+        ev[2 * i].record()
+        run()
+        ev[2 * i + 1].record()
+    torch.cuda.synchronize()
+    return float(np.median([ev[2 * i].elapsed_time(ev[2 * i + 1]) for i in range(n)])) * 1e3
+
+
+def test_heads_time_follows_the_batch():
+    """One request's head costs about the same among 8192 tasks of 1000 outputs
+    as among 16 (a grid over the whole table took 18 times as long)."""
+    w = wl.WORKLOADS[2]
+    W = torch.randn(1000, w.d, device="cuda").to(w.torch_dtype)
+    final, cfg, t = wl.final_norm(w, "cuda"), R.cfg_for(w), {}
+    for n in (16, 8192):
+        n_out = np.full(n, 1000, np.int32)
+        tab = B.HeadTable(n_out, [W] * n, [None] * n, R._POOL["first"])
+        pb = B.Batch(np.array([n // 2], np.int32), np.ones(1, np.int32), n, n_out=n_out)
+        x, out = torch.randn(1, w.d, device="cuda"), torch.empty(1000, device="cuda")
+        ws = torch.empty(B.vfm_workspace_size(cfg, pb.c), dtype=torch.uint8, device="cuda")
+        log(f"head among {n} tasks")
+        t[n] = _us(lambda: B.vfm_head_forward(cfg, final["w"], final["b"], tab.c, pb.c, x, out, ws))
+        log(f"  {t[n]:.1f} us")
+    assert t[8192] < 4 * t[16], t
+
+
 def _rows_of(w, model, task, length, seeds):
     """Layer outputs of requests whose input rows follow from their own seeds,
     in arrival order (one list entry per request)."""
