@@ -296,6 +296,63 @@ def test_decode_rows_same_beside_others(n, max_rank):
     assert torch.equal(run(1), run(n))
 
 
+def _decode_layer(w, model, n_tasks, ids, rows, ctx):
+    """One decode row of each of tasks ids (ascending) in a table of n_tasks,
+    ids[i] with adapter i of the model; returns a callable and its x."""
+    ad = model.adapters[0]
+    at = {int(t): i for i, t in enumerate(ids)}
+    ranks = np.array([int(ad.rank[at[t]]) if t in at else 0 for t in range(n_tasks)], np.int32)
+    factors = {p: ([ad.a(p, at[t]) if t in at else None for t in range(n_tasks)],
+                   [ad.b(p, at[t]) if t in at else None for t in range(n_tasks)]) for p in ad.A}
+    tab = B.LoraTable(n_tasks, ranks, np.full(n_tasks, 2.0), factors, max_rank=ad.max_rank)
+    n = len(ids)
+    start = (np.arange(n) * (ctx + 1)).astype(np.int32)
+    pb = B.Batch(np.asarray(ids, np.int32), np.ones(n, np.int32), n_tasks, ctx_len=np.full(n, ctx, np.int32),
+                 kv_start=start)
+    slots = n * (ctx + 1)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    k, v = (torch.randn(w.n_heads, slots, w.head_dim, generator=g, device="cuda").to(w.torch_dtype) for _ in range(2))
+    x = torch.empty(n, w.d, device="cuda")
+    ws = torch.empty(B.vfm_workspace_size(model.cfg, pb.c, tab.c), dtype=torch.uint8, device="cuda")
+
+    def run():
+        B.vfm_layer_forward(model.cfg, model.c_layers[0], tab.c, pb.c, x, k, v, slots, ws)
+
+    set_rows(x, rows)
+    return run, x, (tab, pb)
+
+
+@pytest.mark.parametrize("n_tasks", [64, 65, 129, 4096, 4097, 9001])
+def test_decode_rows_same_in_a_larger_table(n_tasks):
+    """Decode rows whose split shrink runs in the GEMM's launch find their
+    task in tables up to and past what one and two rounds of the search cover:
+    the same bits as in a table of five, ids at its ends and beside each other."""
+    w = wl.WORKLOADS[5].replace(d=2048, n_heads=16, d_ff=5504, n_tasks=5)
+    model = R.Model(w, n_layers=1, ranks=np.array([8, 16, 0, 32, 16], np.int32), b_std=0.05)
+    rows = seeded_rows(5, w.d, 3)
+    log(f"decode in a table of {n_tasks}")
+    ids = [0, n_tasks // 2, n_tasks // 2 + 1, n_tasks - 2, n_tasks - 1]
+    small, x0, keep0 = _decode_layer(w, model, 5, range(5), rows, 40)
+    large, x1, keep1 = _decode_layer(w, model, n_tasks, ids, rows, 40)
+    small()
+    large()
+    assert x0.isfinite().all() and torch.equal(x0, x1)
+
+
+def test_decode_time_follows_the_batch():
+    """One decode row costs about the same among 8192 tasks as among 64 (a
+    scan of the whole table in every shrink item took 2.3 times as long)."""
+    w = wl.WORKLOADS[5].replace(d=2048, n_heads=16, d_ff=5504, n_tasks=1)
+    model = R.Model(w, n_layers=1, ranks=np.array([8], np.int32), b_std=0.05)
+    t = {}
+    for n in (64, 8192):
+        run, _, keep = _decode_layer(w, model, n, [n // 2], seeded_rows(1, w.d, 3), 100)
+        log(f"decode row among {n} tasks")
+        t[n] = _us(run)
+        log(f"  {t[n]:.1f} us")
+    assert t[8192] < 1.6 * t[64], t
+
+
 @pytest.mark.parametrize("lens", [[129], [150, 106], [333, 200], [512, 70], [900, 123]])
 def test_walked_splits_same_as_split_launch(lens):
     """Prompt batches wide enough that a block walks every K split of its tile
