@@ -575,13 +575,16 @@ __device__ __forceinline__ f32x4 lora_f32(const GemmLora& L, int slot, int m, in
   const int t = L.row_task[m];
   const int r = min(L.rank[t], L.max_rank) & ~7;
   if (r <= 0 || L.B[slot] == nullptr) return s;
-  const float* Bt = (const float*)L.B[slot][t] + (int64_t)nrow * r;
+  // a pointer from the table: read as global memory, not through flat addressing
+  typedef const float __attribute__((address_space(1)))* growp;
+  typedef const f32x4 __attribute__((address_space(1)))* gvecp;
+  const growp Bt = (growp)L.B[slot][t] + (int64_t)nrow * r;
   const float* u = (const float*)L.U + (int64_t)m * L.ldu + L.ucol[slot];
   for (int q = 0; q < r; q += 4) {
     const f32x4 uv = *reinterpret_cast<const f32x4*>(u + q);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const f32x4 bv = *reinterpret_cast<const f32x4*>(Bt + (int64_t)c * r + q);
+      const f32x4 bv = *(gvecp)(Bt + (int64_t)c * r + q);
 #pragma unroll
       for (int e = 0; e < 4; ++e) s[c] = fmaf(uv[e], bv[e], s[c]);
     }
