@@ -6,20 +6,20 @@
 // The paper batches all requests through the shared backbone and then adds
 // each adapter's difference on its own requests (Section 4.2, adapter
 // handling; Fig. 5 (c)).  Here the difference is not a second pass over the
-// output: after the K loop, a tile that holds rows of tasks t0..t1 (rows are
-// sorted by task, so a tile spans a contiguous task range) runs, per task,
-// ceil(r_t / 32) more MFMA steps with A-operand B_t (the task's expand factor,
-// read straight from its device pointer) and B-operand U (the per-row shrink
-// output s_t x A_t^T), masked to that task's rows.  The sum is exactly
-// x W^T + s_t (x A_t^T) B_t^T per row.
+// output: rows are sorted by task, so a tile's rows form runs of one task
+// each, and after the K loop the tile runs more MFMA steps whose operands are
+// U (the per-row shrink output s_t x A_t^T) and B_t (the task's expand factor,
+// read straight from its device pointer), each run meeting its own factor.
+// The sum is exactly x W^T + s_t (x A_t^T) B_t^T per row.
 //
-// bf16 path (gfx950): v_mfma_f32_16x16x32_bf16, 128x128x64 block tile,
-// 4 waves of 64x64, LDS double buffer with an XOR swizzle so that both the
-// 16-byte fragment reads and the row writes are bank-conflict free, global
-// loads for tile k+1 in flight during the MFMAs of tile k.  The weight tile
+// bf16 path (gfx950): v_mfma_f32_16x16x32_bf16 on LDS tiles fed by
+// global_load_lds (gemm_tile.inc): 256-row tiles of 8 waves, or 64- and
+// 128-row ones of 4 where those cannot fill the chip, with an XOR swizzle so
+// that the 16-byte fragment reads are bank-conflict free.  The weight tile
 // feeds the MFMA A slot and the activation tile the B slot, so each lane ends
-// up with 4 consecutive output columns of one row: epilogue stores are 8-byte
-// (bf16) or 16-byte (fp32) vectors.
+// up with 4 consecutive output columns of one row.  Their offsets inside an
+// operand are 32-bit: operands of 2^31 elements or more take a
+// register-staged kernel (gemm_bf16_kernel).
 //
 // fp32 path: fp32 MFMA with small tiles and K split over a block's waves
 // (gemm_f32_kernel), the same epilogues.

@@ -262,6 +262,17 @@ def test_direct_tiles_against_oracle(idx, lens):
     _check_layer(w, out[0], out[1], out[2], out[3], range(len(lens)))
 
 
+def test_operands_of_2_31_elements():
+    """1024 rows x 2^21 MLP columns: the down projection's activations need
+    64-bit offsets and take the kernel for such operands, with adapters of one
+    and two 32-column steps and a bare task."""
+    w = wl.WORKLOADS[2].replace(d=64, n_heads=1, d_ff=1 << 21, n_tasks=3, lora_targets=("q", "up", "down"))
+    log("operands of 2^31 elements")
+    out = _layer_case(w, [2, 0, 1, 2, 0], [1, 9, 500, 4, 510], [16, 0, 40], b_std=0.03)
+    pl = out[1]
+    _check_layer(w, *out, [p for p in range(5) if pl["cu_seqlens"][p + 1] - pl["cu_seqlens"][p] < 10])
+
+
 @pytest.mark.parametrize("n", [1, 3, 33, 64, 65, 128, 129])
 @pytest.mark.parametrize("max_rank", [8, 32, 64])
 def test_decode_rows_same_beside_others(n, max_rank):
