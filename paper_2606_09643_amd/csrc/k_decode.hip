@@ -72,7 +72,7 @@ __device__ __forceinline__ void shrink_split_rows(const Plan& pl, const ShrinkSp
       for (int s = 0; s < NSUB; ++s)
         arow[pp][s] = At + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + 8 * (lane >> 4);
     }
-#pragma unroll 4
+    // (not unrolled by the compiler, whatever it is told: a step waits for its own loads)
     for (int k = k0; k < k1; k += 32) {
       const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xrow + k);
 #pragma unroll

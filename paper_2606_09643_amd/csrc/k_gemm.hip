@@ -368,7 +368,8 @@ __device__ __forceinline__ void epilogue_lds(const GemmArgs& a, char* lds, int m
       }
     }
     __syncthreads();
-#pragma unroll (WM == 2 ? HR * QR / NTH : 4)
+    constexpr int UNROLL = WM == 2 ? HR * QR / NTH : 4;   // `old` is indexed by constants
+#pragma unroll UNROLL
     for (int e = tid; e < HR * QR; e += NTH) {
       const int r = e / QR, q = e % QR;
       const int m = m0 + half * HR + r, n = n0 + q * 4;

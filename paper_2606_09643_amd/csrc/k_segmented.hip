@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256) void shrink_f32_kernel(Plan pl, ShrinkArgs a) 
 #pragma unroll
     for (int s = 0; s < NSUB; ++s)
       ar[s] = (const float*)a.A[p][t] + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + ko;
-#pragma unroll 4
+    // (not unrolled by the compiler, whatever it is told: a step waits for its own loads)
     for (int k = 0; k < kq; k += 16) {
       const f32x4 xv = *reinterpret_cast<const f32x4*>(xr + k);
 #pragma unroll
