@@ -364,14 +364,20 @@ def test_decode_time_follows_the_batch():
     assert t[8192] < 1.6 * t[64], t
 
 
-@pytest.mark.parametrize("lens", [[129], [150, 106], [333, 200], [512, 70], [900, 123]])
-def test_walked_splits_same_as_split_launch(lens):
-    """Prompt batches wide enough that a block walks every K split of its tile
-    (each of its tile shapes, whole and ragged) give a request the bits that
-    the split launch gives it alone (at most 128 rows)."""
-    w = wl.WORKLOADS[4].replace(d=4096, d_ff=11008, n_tasks=3)
+@pytest.mark.parametrize("lens,d,hd,d_ff", [
+    ([129], 4096, 128, 11008), ([150, 106], 4096, 128, 11008), ([257], 4096, 128, 11008), ([333], 4096, 128, 11008),
+    ([300, 200], 4096, 128, 11008), ([333, 200], 4096, 128, 11008), ([512, 70], 4096, 128, 11008),
+    ([900, 123], 4096, 128, 11008), ([200, 57], 2112, 64, 5504), ([400], 2112, 64, 5504), ([450, 250], 2112, 64, 5504),
+    ([800, 200], 2112, 64, 5504)])
+def test_walked_splits_same_as_split_launch(lens, d, hd, d_ff):
+    """From 257 rows on, where a block walks every K split of its tile, a
+    request gets the bits that the split launch gives it alone (at most 128
+    rows): each tile shape of the walk (128 x 128, 128 / 192 / 256 x 192), row
+    and column tiles whole and ragged, and 129 and 256 rows, the edges of the
+    split launch's 256-row tile."""
+    w = wl.WORKLOADS[4].replace(d=d, n_heads=d // hd, head_dim=hd, d_ff=d_ff, n_tasks=3)
     model = R.Model(w, n_layers=1, ranks=np.asarray([16, 0, 8], np.int32), b_std=0.05)
-    log(f"walked splits lens={lens}")
+    log(f"walked splits d={d} lens={lens}")
     alone = _rows_of(w, model, [2], [100], [5])[0]
     whole = _rows_of(w, model, [2] + [0, 1][:len(lens)], [100] + [n - 100 if i == 0 else n for i, n in enumerate(lens)],
                      [5, 6, 7][:len(lens) + 1])[0]
