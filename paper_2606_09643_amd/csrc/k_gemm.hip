@@ -676,15 +676,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   }
 }
 
-// 64x64 tiles where they give every CU a block, else 32x32 (4096 rows x 256
+// 64x64 tiles where they give every CU a block, and a short K every CU two (one
+// block's stores then overlap another's K loop), else 32x32.  4096 rows x 256
 // columns of K = 1024: 27.5 us against 36.0 with 32x32 tiles; 1024 rows, 64
-// such blocks: 11.5 us with 32x32).  SwiGLU's second weight takes the
+// such blocks: 11.5 us with 32x32.  Encoder layers, 32x32 against 64x64 at
+// widths 512 / 1024: 512 rows 119.1 / 276.2 against 119.1 / 270.2 us, 4096 rows
+// 515.8 / 1658 against 460.8 / 1381.  At width 256, products of K = 256 with 256
+// to 511 such blocks: 1024 / 2048 / 4096 rows 92.0 / 122.2 / 191.3 us a layer
+// with 64x64, 88.7 / 117.9 / 188.7 with 32x32.  SwiGLU's second weight takes the
 // accumulators of the larger tile, so it stays at 32x32.
 template <int EPI, bool SW>
 void launch_f32(const GemmArgs& a, hipStream_t s) {
   auto blocks = [&](int b) { return (a.M + b - 1) / b * ((a.N + b - 1) / b); };
   if constexpr (!SW) {
-    if (blocks(64) >= 256) {
+    if (blocks(64) >= (a.K < 512 ? 512 : 256)) {
       hipLaunchKernelGGL((gemm_f32_kernel<EPI, SW, 4, 4>), dim3(blocks(64)), dim3(256), 0, s, a);
       return;
     }
