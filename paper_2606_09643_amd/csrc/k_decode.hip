@@ -482,7 +482,12 @@ void skinny_shape(int N, int K, int* bn, int* nsplit) {
 // decoder's weights.  A block's K step takes what its waves need from barrier
 // to barrier, whatever the depth of the rings; one block per CU runs at a
 // time.  The split launch also writes and reads back nsplit - 1 more slices of
-// 4 M N bytes.  333 rows: QKV 65.0 -> 55.9 us as 128 x 192, gate+up 105.2 ->
+// 4 M N bytes.  Layers of other widths, 257 / 400 / 640 / 1000 rows, split against
+// the rule: 1024 wide 155.9 / 173.0 / 232.3 / 311.4 -> 114.2 / 118.8 / 135.6 /
+// 157.4 us (its other projections direct), 2048 wide 217 / 254 / 346 / 493 -> 186 /
+// 213 / 261 / 319, 8192 wide 1307 / 1426 / 2110 / 2904 -> 1197 / 1326 / 1855 / 2631;
+// none of 28 (1024 to 8192 wide, decoders and encoders) is slower.  333 rows:
+// QKV 65.0 -> 55.9 us as 128 x 192, gate+up 105.2 ->
 // 71.4 as 192 x 192, the finalizes 36.2 / 42.4 -> 28.6 / 35.0; O and down stay
 // split (33.3, 66.4 against 44.1, 108.4).  1000 rows: QKV 135.8 -> 94.9, gate+up
 // 210.2 -> 178.1, O 65.7 -> 49.6, down 131.6 -> 119.0.

@@ -268,7 +268,11 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // is then at most 16 steps: the partials' traffic and the finalize launch cost
 // more than the K split saves (197 rows, K = 768, shrink to result: QKV 30.8
 // -> 16.7 us, O with the norm 24.9 -> 18.7, up 24.1 -> 8.2).  The rule looks
-// at the weight alone, so a row's sums do not depend on the batch.
+// at the weight alone, so a row's sums do not depend on the batch.  Whole
+// layers, split against direct: 1024 wide with 2816 MLP columns 71.1 / 95.7 /
+// 153.7 / 291.5 -> 69.9 / 88.0 / 93.4 / 124.7 us at 1 / 64 / 300 / 1000 rows, 512
+// wide 62.5 -> 55.1 at one; with 1024 MLP columns (O and down both 16 blocks)
+// one row loses, 67.8 -> 71.5, and 16 rows on gain.
 constexpr int VFM_DIRECT_K = 1024;
 
 // ---- small-batch (decode) projections, bf16 only -------------------------
@@ -323,9 +327,8 @@ __device__ inline int64_t kv_slot(const Plan& pl, const KvPages& kp, int p, int 
 
 // Per-task LoRA of a small-batch projection group, applied by the finalize
 // pass: for row m of task t, U = bf16(s_t * sum_c P[c, m, ucol[i] + j]) (the
-// split shrink's partials, four running sums by chunk index mod 4, added
-// pairwise) and
-// column n of slot i gains sum_{j < r_t} U[i][j] B_{t,i}[n', j], n' = the
+// split shrink's partials, in the order that fin_lora_u states) and column n
+// of slot i gains sum_{j < r_t} U[i][j] B_{t,i}[n', j], n' = the
 // column within its slot (SwiGLU: gate columns slot 0, up columns slot 1).
 struct FinLora {
   int enabled;
