@@ -172,17 +172,27 @@ def test_small_batch_rows_same_in_any_tile(idx, d, d_ff, ranks, lens):
         assert torch.equal(alone, whole[i]), f"request {i} of {lens}"
 
 
-@pytest.mark.parametrize("idx,d,d_ff,ranks", [(2, 768, 3072, [16, 8, 16, 0, 8]), (3, 1024, 2816, [64, 8, 16, 0, 40]),
-                                              (4, 1024, 960, [16, 16, 8, 0, 8]), (4, 1024, 960, [32, 8, 32, 16, 24]),
-                                              (4, 1024, 960, [48, 64, 8, 0, 16]), (4, 2048, 5504, [16, 8, 16, 0, 8])])
-@pytest.mark.parametrize("lens", [[1, 2, 1, 3, 1], [70, 30, 1, 40, 200]])
+_SMALL, _MID = ([1, 2, 1, 3, 1], [70, 30, 1, 40, 200]), [700, 300, 100, 17, 400]
+
+
+@pytest.mark.parametrize("idx,d,hd,d_ff,ranks,lens", [
+    *((*c, n) for n in _SMALL for c in (
+        (2, 768, 64, 3072, [16, 8, 16, 0, 8]), (3, 1024, 64, 2816, [64, 8, 16, 0, 40]),
+        (4, 1024, 128, 960, [16, 16, 8, 0, 8]), (4, 1024, 128, 960, [32, 8, 32, 16, 24]),
+        (4, 1024, 128, 960, [48, 64, 8, 0, 16]), (4, 2048, 128, 5504, [16, 8, 16, 0, 8]))),
+    (2, 768, 64, 3072, [16, 8, 16, 0, 8], _MID), (3, 1024, 64, 2816, [64, 8, 16, 0, 40], _MID),
+    (4, 1024, 64, 960, [16, 16, 8, 0, 8], _MID), (4, 1024, 64, 960, [48, 64, 8, 0, 16], _MID),
+    (2, 768, 64, 3072, [16, 8, 16, 0, 8], [1500, 800, 300, 1200, 900]),       # O and down alone: 128-row tiles
+    (2, 768, 64, 3072, [64, 8, 16, 0, 40], [1500, 800, 300, 1200, 900])])
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
-def test_broken_adapter_stays_with_its_task(idx, d, d_ff, ranks, lens, bad):
-    """Small batches: a task whose expand factors hold an infinity or a NaN
-    spoils its own requests only; every other request keeps its bits, in tiles
-    that hold rows of both, LoRA steps of one run and of several."""
-    w = wl.WORKLOADS[idx].replace(d=d, n_heads=d // 128 if idx == 4 else d // 64, d_ff=d_ff, n_tasks=5,
-                                  lora_targets=wl.PROJ if idx == 4 else ("q", "k", "v", "o", "up", "down"))
+def test_broken_adapter_stays_with_its_task(idx, d, hd, d_ff, ranks, lens, bad):
+    """Batches on the 64- and 128-row tiles and on the split path: a task whose
+    expand factors hold an infinity or a NaN spoils its own requests only; every
+    other request keeps its bits, in tiles that hold rows of both, LoRA steps of
+    one run and of several."""
+    w = wl.WORKLOADS[idx].replace(d=d, n_heads=d // hd, head_dim=hd, d_ff=d_ff, n_tasks=5,
+                                  lora_targets=wl.PROJ if idx == 4 else ("o", "down") if sum(lens) > 2000
+                                  else ("q", "k", "v", "o", "up", "down"))
     model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=0.05)
     log(f"broken adapter {w.name} d={d} lens={lens} ranks={ranks} {bad}")
     whole = _rows_of(w, model, [3, 0, 2, 1, 4], lens, [5, 6, 7, 8, 9])
