@@ -480,9 +480,9 @@ hipError_t launch_finalize_norm(int dtype, const FinalizeArgs& a, const void* g,
 #define FN(MC, NT)                                                                                            \
   hipLaunchKernelGGL((finalize_norm_kernel<bf16, MC, NT>), dim3((a.M + 7) / 8 * 8), dim3(NT), 0, s, a,        \
                      (const bf16*)g, (const bf16*)b, kind, eps, (bf16*)h)
-  // by the row's width alone (a row's sums do not depend on the batch); rows of
-  // at most VFM_DIRECT_K columns come from the small-tile GEMM and not here
-  if (a.N <= 4096) FN(1, 1024);
+  // by the row's width alone (a row's sums do not depend on the batch)
+  if (a.N <= 1024) FN(1, 256);
+  else if (a.N <= 4096) FN(1, 1024);
   else FN(2, 1024);
 #undef FN
   return hipGetLastError();
