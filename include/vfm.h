@@ -68,8 +68,8 @@ enum { VFM_EMBED_ROWS = 0, VFM_EMBED_TOKENS = 1, VFM_EMBED_PATCHES = 2 };
 
 /* bf16 batches with fewer rows than this take the small-batch kernels
  * (weight-streaming split-K GEMM whose finalize pass adds each row's LoRA
- * difference, or for K <= 1024 without RoPE one GEMM of small tiles; norms of
- * wide rows by blocks); larger ones take tiles with the LoRA expand fused and
+ * difference, or, with VFM_ATTN_BIDIR and K <= 1024, one GEMM of small tiles;
+ * norms of wide rows by blocks); larger ones take tiles with the LoRA expand fused and
  * wave-per-row norms.  Both fix their
  * summation order from the weight shapes alone, and attention picks its
  * kernel by each request's own length, so a row's output is bit-identical

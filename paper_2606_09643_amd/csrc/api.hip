@@ -361,6 +361,7 @@ int layer_impl(const vfm_cfg& c, const vfm_layer_weights* w, const vfm_lora_tabl
   const bool use_lora = lora && rpad > 0;
 
   const bool skinny = use_skinny(c, pl);
+  const bool direct = c.attn == VFM_ATTN_BIDIR;   // see VFM_DIRECT_K
 
   auto has = [&](int p) { return use_lora && lora->A[p] != nullptr; };
   // One projection group: X [T, K] times the stacked weights (W, then W2
@@ -384,7 +385,7 @@ int layer_impl(const vfm_cfg& c, const vfm_layer_weights* w, const vfm_lora_tabl
     for (int p : projs) any = any || has(p);
     // (with RoPE, the QKV projection of a small batch stays on the split path,
     // whose finalize rotates before the one rounding to bf16)
-    if (!skinny || (K <= VFM_DIRECT_K && !fin_rope.on)) {
+    if (!skinny || (direct && K <= VFM_DIRECT_K && !fin_rope.on)) {
       if (any) {
         ShrinkArgs a = {};
         a.X = X; a.ldx = K; a.K = K; a.U = U; a.ldu = ldu; a.rpad = rpad;

@@ -262,17 +262,21 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 
-// Small bf16 batches: projections whose weight has K of at most this many
-// columns skip the split-K path (split GEMM into fp32 partials, split shrink,
-// finalize) for the shrink and one launch of launch_gemm's tiles, whose K loop
-// is then at most 16 steps: the partials' traffic and the finalize launch cost
-// more than the K split saves (197 rows, K = 768, shrink to result: QKV 30.8
-// -> 16.7 us, O with the norm 24.9 -> 18.7, up 24.1 -> 8.2).  The rule looks
-// at the weight alone, so a row's sums do not depend on the batch.  Whole
-// layers, split against direct: 1024 wide with 2816 MLP columns 71.1 / 95.7 /
-// 153.7 / 291.5 -> 69.9 / 88.0 / 93.4 / 124.7 us at 1 / 64 / 300 / 1000 rows, 512
-// wide 62.5 -> 55.1 at one; with 1024 MLP columns (O and down both 16 blocks)
-// one row loses, 67.8 -> 71.5, and 16 rows on gain.
+// Small bf16 batches of an encoder (bidirectional attention): projections whose
+// weight has K of at most this many columns skip the split-K path (split GEMM
+// into fp32 partials, split shrink, finalize) for the shrink and one launch of
+// launch_gemm's tiles, whose K loop is then at most 16 steps: the partials'
+// traffic and the finalize launch cost more than the K split saves (197 rows,
+// K = 768, shrink to result: QKV 30.8 -> 16.7 us, O with the norm 24.9 -> 18.7,
+// up 24.1 -> 8.2).  The rule looks at the weight and the kind of attention
+// alone, so a row's sums do not depend on the batch.  Whole layers, split
+// against direct: 1024 wide with 2816 MLP columns 71.1 / 95.7 / 153.7 / 291.5 ->
+// 69.9 / 88.0 / 93.4 / 124.7 us at 1 / 64 / 300 / 1000 rows, 512 wide 62.5 -> 55.1
+// at one; with 1024 MLP columns (O and down both 16 blocks) one row loses, 67.8
+// -> 71.5, and 16 rows on gain.  Decoders stay on the split path: a decode
+// step's rows are mostly one per task, and a tile's LoRA steps come one after
+// the other (64 rows of 64 tasks, 1024 wide with 1024 MLP columns, rank 16 / 64:
+// direct 162.7 / 379.6 us, split 88.3 / 130.9).
 constexpr int VFM_DIRECT_K = 1024;
 
 // ---- small-batch (decode) projections, bf16 only -------------------------

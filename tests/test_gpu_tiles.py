@@ -374,6 +374,38 @@ def test_decode_time_follows_the_batch():
     assert t[8192] < 1.6 * t[64], t
 
 
+def _spread(w, model, n_tasks, n, run_of):
+    """Time of a layer over n one-row requests, all of one task or each of its
+    own: {distinct tasks: us}; run_of makes the call for task ids."""
+    t = {}
+    for k in (1, n):
+        ids = np.sort(np.arange(n, dtype=np.int32) * (n_tasks // n) if k == n else np.zeros(n, np.int32))
+        run, keep = run_of(ids)
+        t[k] = _us(run)
+        log(f"  {k} tasks {t[k]:.1f} us")
+    return t
+
+
+def test_narrow_decode_time_of_many_tasks():
+    """64 decode rows of a 1024-wide decoder: each row of a task of its own at
+    rank 64 against all of one task (LoRA steps one task after another in a
+    tile took 4 times as long)."""
+    w = wl.WORKLOADS[5].replace(d=1024, n_heads=8, d_ff=1024, n_tasks=128)
+    model = R.Model(w, n_layers=1, ranks=np.full(128, 64, np.int32), b_std=0.05)
+    log("narrow decode, 64 rows")
+
+    def run_of(ids):
+        ctx = np.full(64, 100, np.int32)
+        pb = B.Batch(ids, np.ones(64, np.int32), 128, ctx_len=ctx, kv_start=(np.arange(64) * 101).astype(np.int32))
+        k, v = (torch.randn(8, 64 * 101, 128, device="cuda").to(w.torch_dtype) for _ in range(2))
+        x = torch.randn(64, w.d, device="cuda")
+        ws = torch.empty(B.vfm_workspace_size(model.cfg, pb.c, model.lora_c(0)), dtype=torch.uint8, device="cuda")
+        return lambda: B.vfm_layer_forward(model.cfg, model.c_layers[0], model.lora_c(0), pb.c, x, k, v, 64 * 101, ws), pb
+
+    t = _spread(w, model, 128, 64, run_of)
+    assert t[64] < 2.5 * t[1], t
+
+
 @pytest.mark.parametrize("lens,d,hd,d_ff", [
     ([129], 4096, 128, 11008), ([150, 106], 4096, 128, 11008), ([257], 4096, 128, 11008), ([333], 4096, 128, 11008),
     ([300, 200], 4096, 128, 11008), ([333, 200], 4096, 128, 11008), ([512, 70], 4096, 128, 11008),
