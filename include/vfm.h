@@ -69,11 +69,11 @@ enum { VFM_EMBED_ROWS = 0, VFM_EMBED_TOKENS = 1, VFM_EMBED_PATCHES = 2 };
 /* bf16 batches with fewer rows than this take the small-batch kernels
  * (weight-streaming split-K GEMM whose finalize pass adds each row's LoRA
  * difference, or, with VFM_ATTN_BIDIR and K <= 1024, one GEMM of small tiles;
- * norms of wide rows by blocks); larger ones take tiles with the LoRA expand fused and
- * wave-per-row norms.  Both fix their
- * summation order from the weight shapes alone, and attention picks its
- * kernel by each request's own length, so a row's output is bit-identical
- * across batches on the same side of this threshold. */
+ * norms of wide rows by blocks); larger ones take tiles with the LoRA expand
+ * fused and wave-per-row norms.  Both fix their summation order from the
+ * configuration and the weight shapes alone, and attention picks its kernel by
+ * each request's own length, so a row's output is bit-identical across batches
+ * on the same side of this threshold. */
 #define VFM_SMALL_BATCH_ROWS 1024
 
 /* Backbone shape.  Supported: d_model = n_heads * head_dim, head_dim in

@@ -387,9 +387,10 @@ def _spread(w, model, n_tasks, n, run_of):
 
 
 def test_narrow_decode_time_of_many_tasks():
-    """64 decode rows of a 1024-wide decoder: each row of a task of its own at
-    rank 64 against all of one task (LoRA steps one task after another in a
-    tile took 4 times as long)."""
+    """64 decode rows of a 1024-wide decoder at rank 64, each row of a task of
+    its own and all of one task: neither much longer than the other (LoRA steps
+    one task after another in a tile: 370 against 129 us; the shrink's 16-row
+    groups one after another: 110 against 192)."""
     w = wl.WORKLOADS[5].replace(d=1024, n_heads=8, d_ff=1024, n_tasks=128)
     model = R.Model(w, n_layers=1, ranks=np.full(128, 64, np.int32), b_std=0.05)
     log("narrow decode, 64 rows")
@@ -403,7 +404,7 @@ def test_narrow_decode_time_of_many_tasks():
         return lambda: B.vfm_layer_forward(model.cfg, model.c_layers[0], model.lora_c(0), pb.c, x, k, v, 64 * 101, ws), pb
 
     t = _spread(w, model, 128, 64, run_of)
-    assert t[64] < 2.5 * t[1], t
+    assert t[64] < 2 * t[1] and t[1] < 1.5 * t[64], t
 
 
 @pytest.mark.parametrize("lens,d,hd,d_ff", [
