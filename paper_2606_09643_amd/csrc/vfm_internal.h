@@ -276,7 +276,10 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // -> 71.5, and 16 rows on gain.  Decoders stay on the split path: a decode
 // step's rows are mostly one per task, and a tile's LoRA steps come one after
 // the other (64 rows of 64 tasks, 1024 wide with 1024 MLP columns, rank 16 / 64:
-// direct 162.7 / 379.6 us, split 88.3 / 130.9).
+// direct 162.7 / 379.6 us, split 88.3 / 130.9).  An encoder's requests of one or
+// two rows, each of another task, lose for the same reason (16 to 128 rows of a
+// 768-wide layer: 1 to 1.3x the split path's time at rank 16, up to 1.8x at rank
+// 64); from 4 rows a request on, and from 256 rows, direct is level or ahead.
 constexpr int VFM_DIRECT_K = 1024;
 
 // ---- small-batch (decode) projections, bf16 only -------------------------
