@@ -71,15 +71,18 @@ __device__ __forceinline__ void shrink_split_rows(const Plan& pl, const ShrinkSp
     typedef const bf16 __attribute__((address_space(1)))* growp;
     typedef const bf16x8 __attribute__((address_space(1)))* gfragp;
     growp arow[NP][NSUB];
-    bool on[NSUB];
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) on[s] = s * 16 + (lane & 15) < rank;
+    bool on[NP][NSUB];
 #pragma unroll
     for (int pp = 0; pp < NP; ++pp) {
       const growp At = (growp)((const void* const __attribute__((address_space(1)))*)a.A[pp0 + pp])[t];
+      // NULL: a projection the task leaves bare (its rows read X and count as zeros)
+      const bool bare = At == nullptr;
+      const growp A0 = bare ? (growp)a.X : At;
 #pragma unroll
-      for (int s = 0; s < NSUB; ++s)
-        arow[pp][s] = At + (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K + 8 * (lane >> 4);
+      for (int s = 0; s < NSUB; ++s) {
+        on[pp][s] = s * 16 + (lane & 15) < rank && !bare;
+        arow[pp][s] = A0 + (bare ? 0 : (int64_t)min(s * 16 + (lane & 15), rank - 1) * a.K) + 8 * (lane >> 4);
+      }
     }
     // (not unrolled by the compiler, whatever it is told: a step waits for its own loads)
     for (int k = k0; k < k1; k += 32) {
@@ -91,7 +94,7 @@ __device__ __forceinline__ void shrink_split_rows(const Plan& pl, const ShrinkSp
 #pragma unroll
         for (int s = 0; s < NSUB; ++s) {
           bf16x8 af = *(gfragp)(arow[pp][s] + k);
-          if (!on[s]) af = bf16x8{};
+          if (!on[pp][s]) af = bf16x8{};
 #pragma unroll
           for (int g = 0; g < NG; ++g) acc[g][pp][s] = mfma16(af, xf[g], acc[g][pp][s]);
         }

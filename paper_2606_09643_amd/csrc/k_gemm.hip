@@ -91,7 +91,7 @@ __device__ __forceinline__ void lora_expand_frags(const GemmArgs& a, int m0, int
           nrow = nb - slot * L.slot_width + (lane & 15);
           nlim = L.slot_width;
         }
-        if (L.B[slot] == nullptr) continue;
+        if (L.B[slot] == nullptr || L.B[slot][t] == nullptr) continue;   // no adapters, or none of this task
         // a pointer from the table: read as global memory, not through flat addressing
         typedef const bf16 __attribute__((address_space(1)))* growp;
         const growp Bt = (growp)L.B[slot][t];
@@ -575,7 +575,7 @@ __device__ __forceinline__ f32x4 lora_f32(const GemmLora& L, int slot, int m, in
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
   const int t = L.row_task[m];
   const int r = min(L.rank[t], L.max_rank) & ~7;
-  if (r <= 0 || L.B[slot] == nullptr) return s;
+  if (r <= 0 || L.B[slot] == nullptr || L.B[slot][t] == nullptr) return s;
   // a pointer from the table: read as global memory, not through flat addressing
   typedef const float __attribute__((address_space(1)))* growp;
   typedef const f32x4 __attribute__((address_space(1)))* gvecp;

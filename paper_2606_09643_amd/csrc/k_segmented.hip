@@ -134,7 +134,8 @@ __global__ __launch_bounds__(64 * NWV) void shrink_bf16_kernel(Plan pl, ShrinkAr
       const int row = prow0 + i * PR;
       if (row < AR) {                                   // row = (pp*NSUB + s2)*16 + j
         const int pp = row / (NSUB * 16), j = row % (NSUB * 16);
-        src0[i] = j < rank ? (const bf16*)a.A[pp][t] + (int64_t)j * a.K + kcl * 8 : nullptr;
+        const bf16* At = (const bf16*)a.A[pp][t];         // NULL: a projection the task leaves bare
+        src0[i] = j < rank && At != nullptr ? At + (int64_t)j * a.K + kcl * 8 : nullptr;
       } else if (row < AR + ROWS) {                     // rows past the tile's end re-read its last row
         src0[i] = X + (int64_t)min(r0 + row - AR, r1 - 1) * a.ldx + kcl * 8;
       } else {
@@ -217,7 +218,8 @@ __global__ __launch_bounds__(256) void shrink_f32_kernel(Plan pl, ShrinkArgs a) 
   if (r0 >= r1) return;                               // block-uniform
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
   const int m = r0 + (lane & 15);
-  const int rank = min(a.rank[t], NSUB * 16) & ~7;
+  // a NULL factor: a projection the task leaves bare
+  const int rank = a.A[p][t] != nullptr ? min(a.rank[t], NSUB * 16) & ~7 : 0;
   f32x4 acc[NSUB];
 #pragma unroll
   for (int s = 0; s < NSUB; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -261,10 +263,10 @@ __global__ __launch_bounds__(256) void expand_bf16_kernel(Plan pl, ExpandArgs a)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rank = min(a.rank[t], a.max_rank) & ~7;
   const int wr0 = r0 + wave * 16;
-  if (rank <= 0 || wr0 >= r1) return;
+  const bf16* Bt = (const bf16*)a.B[t];
+  if (rank <= 0 || wr0 >= r1 || Bt == nullptr) return;
   const int n0 = blockIdx.y * 64;
   const bf16* U = (const bf16*)a.U;
-  const bf16* Bt = (const bf16*)a.B[t];
   f32x4 acc[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -297,10 +299,10 @@ __global__ __launch_bounds__(256) void expand_f32_kernel(Plan pl, ExpandArgs a) 
   int t, r0, r1;
   tile_rows(pl, blockIdx.x, t, r0, r1);
   const int rank = min(a.rank[t], a.max_rank) & ~7;
-  if (rank <= 0) return;
+  const float* Bt = (const float*)a.B[t];
+  if (rank <= 0 || Bt == nullptr) return;
   const int n0 = blockIdx.y * 64;
   const float* U = (const float*)a.U;
-  const float* Bt = (const float*)a.B[t];
   for (int e = threadIdx.x; e < (r1 - r0) * 64; e += 256) {
     const int m = r0 + e / 64, n = n0 + e % 64;
     if (n >= a.N) continue;

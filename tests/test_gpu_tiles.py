@@ -218,6 +218,36 @@ def test_large_batch_rows_same_in_any_tile(idx, more):
     assert torch.equal(base, got)
 
 
+@pytest.mark.parametrize("idx,hd,lens,ranks", [
+    (1, 64, [3, 70, 20], [8, 16, 64]), (2, 64, [3, 70, 20], [8, 16, 64]), (2, 64, [900, 700, 1000], [16, 16, 8]),
+    (2, 64, [900, 700, 1000], [8, 40, 8]), (4, 128, [3, 20, 10], [8, 16, 32]), (4, 128, [60, 20, 90], [8, 16, 64]),
+    (4, 128, [300, 20, 90], [16, 16, 8])])
+def test_task_with_bare_projections(idx, hd, lens, ranks):
+    """A task that has an adapter for some projections of the table only (NULL
+    entries for the others), on every path: the fp32 kernels, the small and the
+    large tiles, the split shrink in the GEMM's launch and in its own."""
+    more = {4: dict(d=1536, d_ff=1856)}.get(idx, {})
+    w = wl.WORKLOADS[idx].replace(n_tasks=3, head_dim=hd, **more)
+    targets = wl.PROJ if w.family == "decoder" else ("q", "k", "v", "o", "up", "down")
+    w = w.replace(n_heads=w.d // hd, lora_targets=targets)
+    has = {0: targets, 1: targets[::2], 2: targets[1:3]}
+    model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=0.03)
+    ad = model.adapters[0]
+    factors = {p: ([ad.a(p, t) if p in has[t] else None for t in range(3)],
+                   [ad.b(p, t) if p in has[t] else None for t in range(3)]) for p in targets}
+    model.lora[0] = B.LoraTable(3, ad.rank, ad.scale, factors, max_rank=ad.max_rank)
+    log(f"bare projections {w.name} lens={lens}")
+    got = _rows_of(w, model, [1, 0, 2], lens, [5, 6, 7])
+    worst = 0.0
+    for i, t in enumerate([1, 0, 2]):
+        rows = seeded_rows(lens[i], w.d, 5 + i)
+        only = {p: (np64(ad.a(p, t)), np64(ad.b(p, t)), float(ad.scale[t])) for p in has[t]}
+        y = O.layer(spec_of(w), oracle_weights(model.layers[0]), only, rows, pos=np.arange(lens[i]))[0]
+        worst = max(worst, O.row_rel_error(got[i].double().numpy(), y))
+    log(f"  max rel err {worst:.3e}")
+    assert worst < tol(w)
+
+
 def _layer_case(w, task, length, ranks, seed=1, b_std=0.05):
     batch = wl.Batch(np.asarray(task, np.int32), np.asarray(length, np.int32), None)
     model = R.Model(w, n_layers=1, ranks=np.asarray(ranks, np.int32), b_std=b_std, seed=seed)
