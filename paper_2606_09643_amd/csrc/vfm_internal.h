@@ -279,7 +279,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // direct 162.7 / 379.6 us, split 88.3 / 130.9).  An encoder's requests of one or
 // two rows, each of another task, lose for the same reason (16 to 128 rows of a
 // 768-wide layer: 1 to 1.3x the split path's time at rank 16, up to 1.8x at rank
-// 64); from 4 rows a request on, and from 256 rows, direct is level or ahead.
+// 64); from 4 rows a request on (8 at rank 64), and from 256 rows, direct is
+// level or ahead.
 constexpr int VFM_DIRECT_K = 1024;
 
 // ---- small-batch (decode) projections, bf16 only -------------------------
